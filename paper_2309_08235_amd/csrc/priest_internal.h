@@ -115,7 +115,7 @@ struct CemArgs {
 struct ProjTaskLaunch {
   const ProjArgs* tasks;
   const int* prefix;
-  int n_tasks, n_blocks, dims, K;
+  int n_tasks, n_blocks, dims, nv, K;
   bool bf16;
   size_t lds_bytes;
 };

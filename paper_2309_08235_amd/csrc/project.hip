@@ -1,8 +1,8 @@
 // Fused projection sweep for gfx950 (MFMA + VALU, state in registers).
 //
 // Work decomposition.  A block owns SPB samples of one problem for the whole
-// projection and has one 64-lane wave per RT consecutive 16-step time blocks
-// (K <= 256).  Sample coefficients live in registers in the layout of the
+// projection and has one 64-lane wave per RT 16-step time blocks (K <= 256).
+// Sample coefficients live in registers in the layout of the
 // 16x16 FP32 MFMA accumulator: column col = AS*sample + axis (AS axis slots
 // per sample: 4, or 2 for 2D so that 8 samples share the 16 columns), row =
 // coefficient (padded to 16), lane l holding rows 4*(l/16)..+3 of column
@@ -11,17 +11,20 @@
 //
 //   forward   p, v, a rows of each of the wave's time blocks = W xi_bar
 //             (one MFMA 16x16x4 accumulation chain per row type over the
-//             k-chunks, W = [P; Pdot; Pddot] rows as A)
-//   transpose quad-local transpose through LDS: each lane then holds every
-//             axis of 4/AS (sample, t) items per time block
+//             k-chunks, W = [P; Pdot; Pddot] rows as A); a row type that
+//             cannot push (budgets, see the whole-horizon shape) is not
+//             evaluated
+//   transpose inside each quad of lanes, by DPP moves: each lane then holds
+//             every axis of 4/AS (sample, t) items per time block
 //   push-out  closed-form alpha/beta/d of each obstacle as a push-out
 //             Delta * max(0, 1/n - 1) (n = scaled distance), summed over the
-//             obstacles that survive a wave-level bounding-box cull;
+//             item's nearest obstacles, kept in registers between iterations;
 //             velocity / acceleration push-outs w * min(0, w_max/|w| - 1)
 //   transpose back to the column layout
 //   RHS       g_partial = W^T delta per 16-step block (MFMA, the sum over t
-//             is the MFMA reduction); the partials of all blocks added in
-//             time-block order through LDS (one barrier)
+//             is the MFMA reduction; row types with no push are skipped); the
+//             partials of all blocks added in time-block order through LDS
+//             (one barrier)
 //   update    lambda += rho g (eq. (15e)); QP of eq. (15g) through the fixed
 //             KKT block, redone identically by every wave (MFMA):
 //               k = 0 : xi_bar = Pi xi + c0 + M11 (lambda + rho g)
@@ -29,6 +32,17 @@
 //             The k > 0 form equals M11 eta + M12 b whenever A xi_bar = b,
 //             which holds after the first step; it avoids cancelling
 //             n_obs |p| against rho F^T F xi_bar in FP32.
+//
+// What bounds it: instruction issue.  A launch of 250 blocks of 7 waves (1000
+// samples, 100 steps) puts two waves on three SIMDs of a CU and one on the
+// fourth; inserted into its loop, a VALU instruction cost 6 cycles, a taken
+// branch 20, a dependent MFMA 36, an LDS round trip 61 and a barrier nothing.
+// So the loop keeps few instructions and branches on the path that paces the
+// barrier: no LDS transposes (they were 24 LDS operations per wave and
+// iteration), no row types that cannot push, no loop over obstacles, half the
+// partial-sum reads in 2D, no coefficient chunk 3 where there is none.  100
+// iterations of 1000 fresh 2D samples, whole call: 224 -> 179 us; a 2D plan of
+// 20 x 100 iterations 4.14 -> 2.96 ms, a 3D one of 2000 samples 6.14 -> 4.13 ms.
 //
 // After the last iteration one more forward + push-out pass evaluates
 // r(xi_bar) and c1 = sum_t |a_t|^2, summed per sample in fixed t order.
@@ -88,22 +102,12 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Transpose buffers: each lane's float4 at 4 * (lane + lane / 8) floats, i.e.
-// 16 bytes of padding after every 8 lanes.  The float4 writes (8 lanes per
-// pass) then cover all 32 banks once, and so do the quad reads of the
-// transposes (one slot of lane 4 q + x for the 8 quads q of a half-wave, x
-// fixed): slot indices 4 q + x + q / 2 are distinct modulo 8.
-constexpr int kXtRow = 288;            // one row type: 64 lanes x 4 + 8 x 4 padding
-constexpr int kXtBlock = 3 * kXtRow;   // p, v, a (or their push-outs)
-__device__ __forceinline__ int xt_at(int lane) { return 4 * (lane + (lane >> 3)); }
-
 struct Layout {  // offsets into dynamic LDS, in floats
-  int rec, xt, gp, fin, hist, cm, mu, L, z, xs, total;
+  int rec, gp, fin, hist, cm, first, mu, L, z, xs, total;
 };
 
-// rec: obstacle records (three float4 arrays of M, structure of arrays); xt:
-// per-wave transpose buffers (kXtBlock floats per 16-step block); gp: double-buffered partial right-hand sides
-// (256 per block); fin: per-(t, sample) residual^2 and c1 of the final pass;
+// rec: obstacle records (three float4 arrays of M, structure of arrays); gp:
+// double-buffered partial right-hand sides (256 per 16-step block); fin: per-(t, sample) residual^2 and c1 of the final pass;
 // cm: per-wave obstacle candidate masks (4 words per 64 obstacles); xs: the
 // block's samples; mu/L/z: sampler staging.  NB = 16-step blocks of the
 // launch, SPB = samples per block.
@@ -114,11 +118,11 @@ __host__ __device__ inline Layout layout(int dims, int nv, int M, int NB, int MB
   const int D = dims * nv, D4 = round4(D);
   int o = 0;
   l.rec = o; o += 12 * M;
-  l.xt = o;  o += NB * kXtBlock;
   l.gp = o;  o += 2 * MB * 256;
   l.fin = o; o += 2 * 16 * NB * SPB;
   l.hist = o; o += 2 * 16 * NB * SPB;
   l.cm = o;  o += NB * 4 * ((M + 63) / 64);
+  l.first = o; o += 2 * 256;
   l.xs = o;  o += SPB * D4;
   l.mu = o;
   l.L = o + D4;
@@ -148,12 +152,6 @@ __host__ __device__ inline Layout layout(int dims, int nv, int M, int NB, int MB
 // item, where the push-out is exactly 0, so culling does not change results.
 // ---------------------------------------------------------------------------
 constexpr float kTiny = 1.0e-36f;
-
-// Obstacle candidates processed together in the push-out loop.
-#ifndef PRIEST_CAND_UNROLL
-#define PRIEST_CAND_UNROLL 1
-#endif
-constexpr int kCandUnroll = PRIEST_CAND_UNROLL;
 
 // Wave-wide min / max: DPP within each row of 16 lanes (xor 1, xor 2,
 // rotate 4, rotate 8), then the four row results combined as uniform values.
@@ -195,26 +193,6 @@ struct Rec {  // one obstacle record held in (uniform) registers
   float mab;  // smaller semi-axis (3D; read only for clearance bounds)
   bool moving;
 };
-
-// Record of lane b broadcast to the wave; only the fields the push-out of a
-// DIMS-dimensional, static or moving obstacle reads.
-template <int DIMS>
-__device__ __forceinline__ Rec rec_from_lane(const float4& R0, const float4& R1, const float4& R2,
-                                             int b, bool moving) {
-  Rec r;
-  r.moving = moving;
-  r.cx = lane_f(R0.x, b);
-  r.cy = lane_f(R0.y, b);
-  r.cz = (DIMS == 3) ? lane_f(R0.z, b) : 0.0f;
-  r.vx = moving ? lane_f(R1.x, b) : 0.0f;
-  r.vy = moving ? lane_f(R1.y, b) : 0.0f;
-  r.vz = (moving && DIMS == 3) ? lane_f(R1.z, b) : 0.0f;
-  r.a = (DIMS == 2) ? lane_f(R2.x, b) : 0.0f;
-  r.a2 = (DIMS == 2) ? lane_f(R2.y, b) : 0.0f;
-  r.ia2 = (DIMS == 3) ? lane_f(R2.z, b) : 0.0f;
-  r.ib2 = (DIMS == 3) ? lane_f(R2.w, b) : 0.0f;
-  return r;
-}
 
 __device__ __forceinline__ Rec rec_from_lds(const float4* rec, int M, int j) {
   const float4 R0 = rec[j], R1 = rec[M + j], R2 = rec[2 * M + j];
@@ -523,222 +501,75 @@ __device__ void build_records(const float* obs, int M, int t, int nt, float4* re
 // k-chunk r = 3 of every product over coefficients is zero and is skipped.
 __device__ __forceinline__ int coef_of(int q, int r) { return r < 3 ? 3 * q + r : 12 + q; }
 
-// Groups of 64 obstacles whose candidate masks stay in (scalar) registers;
-// the masks of further groups live in LDS.
-constexpr int kRegGroups = 2;
-
-// Per-wave memory of the last obstacle cull: every item's position when the
-// candidate sets were built, the displacement (squared) up to which they stay
-// valid, and the candidate and moving bits of the first kRegGroups groups of
-// 64 obstacles (wave-uniform).  Masks of later groups live in LDS (4 words
-// per group).
-template <int NI, int DIMS, int REG = kRegGroups>
-struct CullCache {
-  float pref[NI][DIMS];
-  float lim2;
-  bool valid;
-  uint32_t nok;    // valid items of the wave (wave-uniform)
-  uint32_t pairs;  // (item, obstacle) pairs evaluated by the wave so far
-  bool rebuilt;    // the last call built new candidate sets
-  unsigned long long cm[REG > 0 ? REG : 1], mv[REG > 0 ? REG : 1];
-};
-
-// Growth of the candidate radius that lets a candidate set be reused: an
-// obstacle is a candidate if it may come within (1 + kSlack) * cull of the
-// wave's box, and the set is reused while no item has moved farther than
-// kSlack * (smallest cull radius) from where it was when the set was built.
-// A skipped obstacle then stays farther than its cull radius from every item,
-// where its push-out is exactly zero.
+// Reach of the obstacle search, in units of kSlack * (smallest cull radius of
+// the scene): an obstacle is near an item if its cull sphere comes within one
+// unit of it, and the search looks kReach units far.  The more slots an item
+// fills, the farther the nearest obstacle it left out, hence the longer it may
+// move before the next search; kRoomy units of room are enough to leave the
+// remaining slots empty.  (16, 8), (8, 4), (32, 8), (32, 16) and (12, 6): a
+// 1000-sample 2D projection of 100 iterations took 179, 194, 183, 181 and
+// 186 us, a 20 x 100 plan 2.96, 2.95, 2.97, 3.04 and 2.94 ms.
 #ifndef PRIEST_CULL_SLACK
 #define PRIEST_CULL_SLACK 0.25f
 #endif
 constexpr float kSlack = PRIEST_CULL_SLACK;
+constexpr float kReach = 16.0f, kRoomy = 8.0f;
 
-// Obstacle push-outs of this lane's NI items, summed over obstacles, with
-// wave-level culling.  tmid / thalf: centre and half-width of the wave's time
-// window.  Candidates are added in one canonical order: per group of 64, the
-// static obstacles by index, then the moving ones by index.
-template <int DIMS, bool LAST, int NI, bool HIST = false, bool TRAJ = false, int REG = kRegGroups>
-__device__ __forceinline__ void obstacle_pushes(const float4* rec, int M, const float tt[NI],
-                                                const float tmid[4], const float thalf[4],
-                                                const bool ok[NI],
-                                                const float p[NI][DIMS], float S[NI][DIMS],
-                                                float r2[NI], int lane, CullCache<NI, DIMS, REG>& cc,
-                                                uint32_t* wm, const float* opath = nullptr,
-                                                const int* tstep = nullptr, int K = 0) {
-  // records of the first group, issued before anything waits on LDS
-  const float4 zr = make_float4(0, 0, 0, 0);
-  // (lanes past the scene load the last record: only lanes of obstacles are
-  // ever read, and unconditional loads keep the compiler from putting each one
-  // under a branch of its own)
-  auto clampj = [M](int j) { return j < M ? j : M - 1; };
-  float4 G0 = zr, G1 = zr, G2 = zr;
-  if (M > 0) {
-    const int l0 = clampj(lane);
-    G0 = rec[l0];
-    G1 = rec[M + l0];
-    G2 = rec[2 * M + l0];
+// Obstacles an item keeps between iterations: its nearest ones, in registers.
+constexpr int lane_slots(int dims) { return dims == 2 ? 4 : 3; }
+
+// One 16-step time block of a wave of the time-split shapes: its items, and
+// the memory of its last obstacle search: every item's position at that time
+// and how far it may move before the search has to be made again, and each
+// item's nearest obstacles, as centres at the item's time and semi-axis terms.
+// A slot without an obstacle, and every slot of an item that is not valid,
+// holds an obstacle that cannot push.
+template <int NI, int DIMS>
+struct TimeBlock {
+  static constexpr int L = lane_slots(DIMS);
+  int t[NI];           // the items' steps
+  float tt[NI];        // and times
+  bool ok[NI];
+  float tmid[4];       // middle of the time window of each row of 16 lanes
+  float pref[NI][DIMS], lim[NI];
+  uint32_t nok;        // valid items (wave-uniform)
+  uint32_t npairs;     // pairs of one evaluation (kept only while pairs are counted)
+  int depth;           // slots to evaluate; 0: no item is near anything; L + 1: the wave's masks
+  float c[L][NI][DIMS];                       // centre
+  float u[L][NI], v[DIMS == 3 ? L : 1][NI];   // a (2D); 1/a^2, 1/b^2 (3D)
+};
+
+// Scene of a tile: records in LDS, path obstacles in memory.
+struct Scene {
+  const float4* rec;
+  const float* path;
+  int M, K;
+  float unit;    // kSlack * (smallest cull radius of the scene)
+  float thalf;   // half the time window of a row of 16 lanes
+};
+
+// Centre of obstacle j at item i's time (a static obstacle's comes unchanged).
+template <int DIMS, bool TRAJ, int NI>
+__device__ __forceinline__ void centre_at(const Scene& sc, const TimeBlock<NI, DIMS>& tb, int i, int j,
+                                          const float c[3], const float v[3], float oc[DIMS]) {
+  if constexpr (TRAJ) {
+    const float* pt = sc.path + static_cast<int64_t>(j) * (sc.K * DIMS + 2) + min(tb.t[i], sc.K - 1) * DIMS;
+#pragma unroll
+    for (int x = 0; x < DIMS; ++x) oc[x] = pt[x];
+  } else {
+#pragma unroll
+    for (int x = 0; x < DIMS; ++x) oc[x] = fmaf(v[x], tb.tt[i], c[x]);
   }
-  // reuse the candidate sets if every item is still within the slack
-  bool reuse = false;
-  if (cc.valid) {
-    bool far = false;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      float d2 = 0.0f;
-#pragma unroll
-      for (int x = 0; x < DIMS; ++x) {
-        const float e = p[i][x] - cc.pref[i][x];
-        d2 = fmaf(e, e, d2);
-      }
-      far = far || (ok[i] && !(d2 <= cc.lim2));
-    }
-    reuse = __ballot(far) == 0ull;
-  }
-  cc.rebuilt = !reuse;
-  if (!reuse) {
-    // one box per row of 16 lanes (the items of 4 time steps): an obstacle is
-    // a candidate if it may come near any of the four
-    float lo[DIMS][4], hi[DIMS][4];
-#pragma unroll
-    for (int x = 0; x < DIMS; ++x) {
-      float mn = INFINITY, mx = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        mn = fminf(mn, ok[i] ? p[i][x] : INFINITY);
-        mx = fmaxf(mx, ok[i] ? p[i][x] : -INFINITY);
-      }
-      row_min4(mn, lo[x]);
-      row_max4(mx, hi[x]);
-    }
-    float cmin = INFINITY;
-    auto cull_group = [&](int g, float4 R0, float4 R1, unsigned long long& mask,
-                          unsigned long long& moving) {
-      const int j = 64 * g + lane;
-      bool cand = false, mv = false;
-      if (j < M) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          // (paths: the sphere around the whole path, grown by its radius)
-          const float oc[3] = {TRAJ ? R0.x : fmaf(R1.x, tmid[q], R0.x),
-                               TRAJ ? R0.y : fmaf(R1.y, tmid[q], R0.y),
-                               TRAJ ? R0.z : fmaf(R1.z, tmid[q], R0.z)};
-          float d2 = 0.0f;
-#pragma unroll
-          for (int x = 0; x < DIMS; ++x) {
-            const float e = fmaxf(fmaxf(lo[x][q] - oc[x], oc[x] - hi[x][q]), 0.0f);
-            d2 = fmaf(e, e, d2);
-          }
-          const float rr = TRAJ ? fmaf(R0.w, 1.0f + kSlack, R1.x)
-                                : fmaf(R1.w, thalf[q], R0.w * (1.0f + kSlack));
-          cand = cand || (d2 < rr * rr);
-        }
-        mv = !TRAJ && R1.w != 0.0f;
-        cmin = fminf(cmin, R0.w);
-      }
-      mask = __ballot(cand);
-      moving = __ballot(cand && mv);
-    };
-#pragma unroll
-    for (int g = 0; g < REG; ++g) {
-      cc.cm[g] = 0ull;
-      cc.mv[g] = 0ull;
-      if (64 * g < M) {
-        const int j = 64 * g + lane;
-        const float4 R0 = g == 0 ? G0 : rec[clampj(j)];
-        const float4 R1 = g == 0 ? G1 : rec[M + clampj(j)];
-        cull_group(g, R0, R1, cc.cm[g], cc.mv[g]);
-      }
-    }
-    for (int g = REG; 64 * g < M; ++g) {
-      const int j = 64 * g + lane;
-      unsigned long long mask, moving;
-      cull_group(g, rec[clampj(j)], rec[M + clampj(j)], mask, moving);
-      if (lane == 0) {
-        wm[4 * g + 0] = static_cast<uint32_t>(mask);
-        wm[4 * g + 1] = static_cast<uint32_t>(mask >> 32);
-        wm[4 * g + 2] = static_cast<uint32_t>(moving);
-        wm[4 * g + 3] = static_cast<uint32_t>(moving >> 32);
-      }
-    }
-    const float lim = kSlack * wave_min(cmin);
-    cc.lim2 = lim * lim;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int x = 0; x < DIMS; ++x) cc.pref[i][x] = p[i][x];
-    cc.valid = true;
-    if (M > 64 * REG) wave_lds_sync();
-  }
-  uint32_t ncand = 0;
-  // the candidates of one group, kCandUnroll at a time (their offsets and
-  // factors are independent), added in the canonical order, the tail one at a
-  // time; R0..R2 hold the group's records, obstacle 64 g + lane in this lane
-  auto group = [&](int base, unsigned long long cmask, unsigned long long mvmask, float4 R0,
-                   float4 R1, float4 R2) {
-    if constexpr (TRAJ) {
-      // obstacle positions at each item's own time step, read from the path
-      unsigned long long mask = cmask;
-      while (mask) {
-        const int b = __builtin_ctzll(mask);
-        mask &= mask - 1;
-        Rec o = rec_of_lane<DIMS, false>(R0, R1, R2, b);
-        const float* path = opath + static_cast<int64_t>(base + b) * (K * DIMS + 2);
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-          const float* pt = path + min(tstep[i], K - 1) * DIMS;
-          o.cx = pt[0];
-          o.cy = pt[1];
-          if constexpr (DIMS == 3) o.cz = pt[2];
-          pair_add<DIMS, LAST || HIST>(o, pair_term<DIMS, LAST, false>(o, tt[i], p[i]), S[i], r2[i]);
-        }
-      }
-      return;
-    }
-    auto run = [&](unsigned long long mask, auto moving_tag) {
-      constexpr bool MV = decltype(moving_tag)::value;
-      while (mask) {
-        if (__builtin_popcountll(mask) >= kCandUnroll) {
-          Rec o[kCandUnroll];
-#pragma unroll
-          for (int u = 0; u < kCandUnroll; ++u) {
-            o[u] = rec_of_lane<DIMS, MV>(R0, R1, R2, __builtin_ctzll(mask));
-            mask &= mask - 1;
-          }
-          PairTerm<DIMS> tm[kCandUnroll][NI];
-#pragma unroll
-          for (int u = 0; u < kCandUnroll; ++u)
-#pragma unroll
-            for (int i = 0; i < NI; ++i) tm[u][i] = pair_term<DIMS, LAST, MV>(o[u], tt[i], p[i]);
-#pragma unroll
-          for (int u = 0; u < kCandUnroll; ++u)
-#pragma unroll
-            for (int i = 0; i < NI; ++i) pair_add<DIMS, LAST || HIST>(o[u], tm[u][i], S[i], r2[i]);
-        } else {
-          const Rec o0 = rec_of_lane<DIMS, MV>(R0, R1, R2, __builtin_ctzll(mask));
-          mask &= mask - 1;
-#pragma unroll
-          for (int i = 0; i < NI; ++i)
-            pair_add<DIMS, LAST || HIST>(o0, pair_term<DIMS, LAST, MV>(o0, tt[i], p[i]), S[i], r2[i]);
-        }
-      }
-    };
-    run(cmask & ~mvmask, std::false_type{});
-    run(mvmask, std::true_type{});
-  };
-#pragma unroll
-  for (int g = 0; g < REG; ++g) {
-    const unsigned long long cmask = cc.cm[g];
-    ncand += static_cast<uint32_t>(__builtin_popcountll(cmask));
-    if (!cmask) continue;
-    if (g == 0) {
-      group(0, cmask, cc.mv[0], G0, G1, G2);
-    } else {
-      const int j = 64 * g + lane;
-      group(64 * g, cmask, cc.mv[g], rec[clampj(j)], rec[M + clampj(j)], rec[2 * M + clampj(j)]);
-    }
-  }
-  for (int g = REG; 64 * g < M; ++g) {
+}
+
+// Calls fn(record, cull radius, index, moving) for the obstacles named by the
+// wave's masks wm (4 words per group of 64: candidates, moving ones), all
+// wave-uniform, in the canonical order: per group the static ones by index,
+// then the moving ones by index.  A static obstacle's record has velocity 0.
+template <int DIMS, typename F>
+__device__ __forceinline__ void each_candidate(const Scene& sc, const uint32_t* wm, int lane, F fn) {
+  const int M = sc.M;
+  for (int g = 0; 64 * g < M; ++g) {
     const uint4 m4 = *reinterpret_cast<const uint4*>(wm + 4 * g);
     // (readfirstlane returns int: widen through uint32_t, not sign-extended)
     auto u64 = [](uint32_t lo, uint32_t hi) {
@@ -746,61 +577,374 @@ __device__ __forceinline__ void obstacle_pushes(const float4* rec, int M, const 
              (static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(hi)))
               << 32);
     };
-    const unsigned long long cmask = u64(m4.x, m4.y);
-    ncand += static_cast<uint32_t>(__builtin_popcountll(cmask));
-    if (!cmask) continue;
-    const int j = 64 * g + lane;
-    group(64 * g, cmask, u64(m4.z, m4.w), rec[clampj(j)], rec[M + clampj(j)],
-          rec[2 * M + clampj(j)]);
-  }
-  cc.pairs += ncand * cc.nok;
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-    if (!ok[i]) {
-#pragma unroll
-      for (int x = 0; x < DIMS; ++x) S[i][x] = 0.0f;
-      r2[i] = 0.0f;
+    const unsigned long long cm = u64(m4.x, m4.y), mv = u64(m4.z, m4.w);
+    if (!cm) continue;
+    const int j = min(64 * g + lane, M - 1);
+    const float4 R0 = sc.rec[j], R1 = sc.rec[M + j], R2 = sc.rec[2 * M + j];
+#pragma unroll 1
+    for (int moving = 0; moving < 2; ++moving) {
+      unsigned long long mask = moving ? mv : cm & ~mv;
+      while (mask) {
+        const int b = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        Rec o = rec_of_lane<DIMS, true>(R0, R1, R2, b);
+        if (!moving) o.vx = o.vy = o.vz = 0.0f;
+        fn(o, lane_f(R0.w, b), 64 * g + b, moving);
+      }
     }
+  }
 }
 
-template <int DIMS, bool LAST, int NI, bool HIST = false, bool TRAJ = false, int REG = kRegGroups>
-__device__ __forceinline__ void item_push(const float4* rec, int M, const float tt[NI],
-                                          const float tmid[4], const float thalf[4],
-                                          const bool ok[NI], const float p[NI][DIMS],
-                                          const float v[NI][DIMS], const float ac[NI][DIMS],
-                                          float vmax, float amax, const Box& box,
-                                          float S[NI][DIMS], float dv[NI][DIMS], float da[NI][DIMS],
-                                          float r2[NI], int lane, CullCache<NI, DIMS, REG>& cc,
-                                          uint32_t* wm, const float* opath = nullptr,
-                                          const int* tstep = nullptr, int K = 0) {
+// Whether every item is still within the reach of the last search.
+template <int DIMS, int NI>
+__device__ __forceinline__ bool still_valid(const TimeBlock<NI, DIMS>& tb, const float p[NI][DIMS]) {
+  bool far = false;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    float d2 = 0.0f;
+#pragma unroll
+    for (int x = 0; x < DIMS; ++x) {
+      const float e = p[i][x] - tb.pref[i][x];
+      d2 = fmaf(e, e, d2);
+    }
+    // (no search yet: lim < 0)
+    far = far || (tb.ok[i] && !(d2 <= tb.lim[i] * fabsf(tb.lim[i])));
+  }
+  return __ballot(far) == 0ull;
+}
+
+// Obstacle search of one time block.
+//
+// First the obstacles that may come near the boxes around the items, one box
+// per row of 16 lanes (the items of 4 time steps); every item then keeps, of
+// those, the L with the smallest gap (distance from the item at its own time to
+// the cull sphere).  Until an item has moved by the gap of the nearest obstacle
+// that it left out, no other obstacle can push it, so an evaluation is a few
+// independent register-only terms, where a loop over all candidates of the wave
+// (ten and more, one dependent rsq each) paced every barrier.  If some item has
+// more than L obstacles within one unit, the wave's candidates are evaluated
+// for every item instead.
+template <int DIMS, bool TRAJ, int NI>
+__device__ __forceinline__ void search_obstacles(const Scene& sc, TimeBlock<NI, DIMS>& tb,
+                                                 const float p[NI][DIMS], int lane, uint32_t* wm,
+                                                 bool count) {
+  constexpr int L = TimeBlock<NI, DIMS>::L;
+  const int M = sc.M;
+  const float reach = sc.unit * kReach;
+  float lo[DIMS][4], hi[DIMS][4];
+#pragma unroll
+  for (int x = 0; x < DIMS; ++x) {
+    float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      mn = fminf(mn, tb.ok[i] ? p[i][x] : INFINITY);
+      mx = fmaxf(mx, tb.ok[i] ? p[i][x] : -INFINITY);
+    }
+    row_min4(mn, lo[x]);
+    row_max4(mx, hi[x]);
+  }
+  uint32_t ncand = 0;
+#pragma unroll 1
+  for (int g = 0; 64 * g < M; ++g) {
+    // (lanes past the scene load the last record)
+    const int j = min(64 * g + lane, M - 1);
+    const float4 R0 = sc.rec[j], R1 = sc.rec[M + j];
+    bool cand = false;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      // (paths: the sphere around the whole path, grown by its radius)
+      const float oc[3] = {TRAJ ? R0.x : fmaf(R1.x, tb.tmid[q], R0.x),
+                           TRAJ ? R0.y : fmaf(R1.y, tb.tmid[q], R0.y),
+                           TRAJ ? R0.z : fmaf(R1.z, tb.tmid[q], R0.z)};
+      float d2 = 0.0f;
+#pragma unroll
+      for (int x = 0; x < DIMS; ++x) {
+        const float e = fmaxf(fmaxf(lo[x][q] - oc[x], oc[x] - hi[x][q]), 0.0f);
+        d2 = fmaf(e, e, d2);
+      }
+      const float rr = TRAJ ? R0.w + reach + R1.x : fmaf(R1.w, sc.thalf, R0.w + reach);
+      cand = cand || (d2 < rr * rr);
+    }
+    cand = cand && 64 * g + lane < M;
+    const unsigned long long mask = __ballot(cand), moving = __ballot(cand && !TRAJ && R1.w != 0.0f);
+    ncand += static_cast<uint32_t>(__builtin_popcountll(mask));
+    if (lane == 0)
+      *reinterpret_cast<uint4*>(wm + 4 * g) =
+          make_uint4(static_cast<uint32_t>(mask), static_cast<uint32_t>(mask >> 32),
+                     static_cast<uint32_t>(moving), static_cast<uint32_t>(moving >> 32));
+  }
+  wave_lds_sync();
+  // the L + 1 smallest gaps of every item, ascending: the gap's leading bits
+  // above the obstacle's rank in the canonical order (11 bits; dropping them
+  // shortens the gap by less than 2^-11 of it)
+  uint32_t key[NI][L + 1];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int k = 0; k <= L; ++k) key[i][k] = ~0u;
+  each_candidate<DIMS>(sc, wm, lane, [&](const Rec& o, float cull, int j, int moving) {
+    const float c[3] = {o.cx, o.cy, o.cz}, v[3] = {o.vx, o.vy, o.vz};
+    const uint32_t rank = static_cast<uint32_t>(((j >> 6) << 7) | (moving << 6) | (j & 63));
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      float oc[DIMS], d2 = 0.0f;
+      centre_at<DIMS, TRAJ>(sc, tb, i, j, c, v, oc);
+#pragma unroll
+      for (int x = 0; x < DIMS; ++x) {
+        const float e = p[i][x] - oc[x];
+        d2 = fmaf(e, e, d2);
+      }
+      // (a distance that is not a finite number counts as none at all)
+      const float gap = d2 < INFINITY ? fmaxf(fmaf(__builtin_amdgcn_sqrtf(d2), 0.999999f, -cull), 0.0f) : 0.0f;
+      uint32_t t = (__float_as_uint(gap) & ~2047u) | rank;
+#pragma unroll
+      for (int k = 0; k <= L; ++k) {
+        const uint32_t a = key[i][k] < t ? key[i][k] : t;
+        t = key[i][k] < t ? t : key[i][k];
+        key[i][k] = a;
+      }
+    }
+  });
+  auto gap_of = [&](uint32_t k) { return k == ~0u ? INFINITY : __uint_as_float(k & ~2047u); };
+  // slots to evaluate
+  bool crowd = false, near = false, roomy1 = true, roomy2 = true;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    near = near || (tb.ok[i] && gap_of(key[i][0]) < sc.unit);
+    crowd = crowd || (tb.ok[i] && gap_of(key[i][L]) < sc.unit);
+    roomy1 = roomy1 && (!tb.ok[i] || gap_of(key[i][1]) >= sc.unit * kRoomy);
+    roomy2 = roomy2 && (!tb.ok[i] || gap_of(key[i][2]) >= sc.unit * kRoomy);
+  }
+  tb.depth = __ballot(near) == 0ull      ? 0
+             : __ballot(crowd) != 0ull   ? L + 1
+             : __ballot(!roomy1) == 0ull ? 1
+             : __ballot(!roomy2) == 0ull ? 2
+                                         : L;
+  int n = 0;
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
 #pragma unroll
-    for (int x = 0; x < DIMS; ++x) { S[i][x] = 0.0f; dv[i][x] = 0.0f; da[i][x] = 0.0f; }
-    r2[i] = 0.0f;
-  }
-  obstacle_pushes<DIMS, LAST, NI, HIST, TRAJ, REG>(rec, M, tt, tmid, thalf, ok, p, S, r2, lane, cc,
-                                                    wm, opath, tstep, K);
+    for (int x = 0; x < DIMS; ++x) tb.pref[i][x] = p[i][x];
+    float gap = gap_of(key[i][L]);  // the nearest obstacle left out
+    uint32_t rk[L];
 #pragma unroll
-  for (int i = 0; i < NI; ++i)
-    if (ok[i]) {
-      bound_push<DIMS>(v[i], vmax, dv[i], r2[i]);
-      bound_push<DIMS>(ac[i], amax, da[i], r2[i]);
+    for (int k = L - 1; k >= 0; --k) {
+      gap = tb.depth == k ? gap_of(key[i][k]) : gap;
+      rk[k] = (tb.ok[i] && k < tb.depth && key[i][k] != ~0u) ? (key[i][k] & 2047u) : ~0u;
+      n += rk[k] != ~0u ? 1 : 0;
     }
-  // workspace bounds: rows -P and P of G, whose targets min(tau, G xi_bar)
-  // add clamp(p, lo, hi) - p to the position rows
-  if (box.on) {
+    tb.lim[i] = tb.depth > L ? reach : fminf(gap, reach);
+    // the slots, in the canonical order
+#pragma unroll
+    for (int m = 1; m < L; ++m)
+#pragma unroll
+      for (int k = m; k > 0; --k) {
+        const uint32_t a = rk[k - 1] < rk[k] ? rk[k - 1] : rk[k];
+        rk[k] = rk[k - 1] < rk[k] ? rk[k] : rk[k - 1];
+        rk[k - 1] = a;
+      }
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+      if (k >= tb.depth) break;
+      const bool has = rk[k] != ~0u;
+      const int j = has ? static_cast<int>(((rk[k] >> 7) << 6) | (rk[k] & 63u)) : 0;
+      const float4 R0 = sc.rec[j], R1 = sc.rec[M + j], R2 = sc.rec[2 * M + j];
+      const bool mv = rk[k] & 64u;
+      const float c[3] = {R0.x, R0.y, R0.z};
+      const float v[3] = {mv ? R1.x : 0.0f, mv ? R1.y : 0.0f, mv ? R1.z : 0.0f};
+      float oc[DIMS];
+      centre_at<DIMS, TRAJ>(sc, tb, i, j, c, v, oc);
+#pragma unroll
+      for (int x = 0; x < DIMS; ++x) tb.c[k][i][x] = has ? oc[x] : 1.0e15f;
+      tb.u[k][i] = DIMS == 3 ? (has ? R2.z : 1.0f) : (has ? R2.x : 0.0f);
+      if constexpr (DIMS == 3) tb.v[k][i] = has ? R2.w : 1.0f;
+    }
+  }
+  if (count) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) n += __shfl_xor(n, m, 64);
+    tb.npairs = tb.depth > L ? ncand * tb.nok : static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(n));
+  }
+}
+
+// Obstacle push-outs of one time block's items, summed over the obstacles in
+// the canonical order; an obstacle that is left out pushes by exactly zero.
+template <int DIMS, bool LAST, bool ACC, bool TRAJ, int NI>
+__device__ __forceinline__ void obstacle_pushes(const Scene& sc, const TimeBlock<NI, DIMS>& tb,
+                                                const float p[NI][DIMS], float S[NI][DIMS], float r2[NI],
+                                                int lane, const uint32_t* wm) {
+  constexpr int L = TimeBlock<NI, DIMS>::L;
+  if (__builtin_expect(tb.depth > L, 0)) {
+    each_candidate<DIMS>(sc, wm, lane, [&](const Rec& o0, float, int j, int) {
+      const float c[3] = {o0.cx, o0.cy, o0.cz}, v[3] = {o0.vx, o0.vy, o0.vz};
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        Rec o = o0;
+        float oc[DIMS];
+        centre_at<DIMS, TRAJ>(sc, tb, i, j, c, v, oc);
+        o.cx = oc[0];
+        o.cy = oc[1];
+        if constexpr (DIMS == 3) o.cz = oc[DIMS - 1];
+        pair_add<DIMS, ACC>(o, pair_term<DIMS, LAST, false>(o, tb.tt[i], p[i]), S[i], r2[i]);
+      }
+    });
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-      if (ok[i]) {
+      if (!tb.ok[i]) {
 #pragma unroll
-        for (int x = 0; x < DIMS; ++x) {
-          const float e = fminf(fmaxf(p[i][x], box.lo[x]), box.hi[x]) - p[i][x];
-          S[i][x] += e;
-          r2[i] = fmaf(e, e, r2[i]);
-        }
+        for (int x = 0; x < DIMS; ++x) S[i][x] = 0.0f;
+        r2[i] = 0.0f;
       }
+    return;
   }
+  auto slots = [&](auto first_tag, auto n_tag) {
+    constexpr int F = decltype(first_tag)::value, N = decltype(n_tag)::value;
+    Rec o[N][NI];
+    PairTerm<DIMS> tm[N][NI];
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        Rec& q = o[k][i];
+        q = Rec{};
+        q.cx = tb.c[F + k][i][0];
+        q.cy = tb.c[F + k][i][1];
+        if constexpr (DIMS == 3) {
+          q.cz = tb.c[F + k][i][2];
+          q.ia2 = tb.u[F + k][i];
+          q.ib2 = tb.v[F + k][i];
+        } else {
+          q.a = tb.u[F + k][i];
+          q.a2 = q.a * q.a;
+        }
+        tm[k][i] = pair_term<DIMS, LAST, false>(q, tb.tt[i], p[i]);
+      }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) pair_add<DIMS, ACC>(o[k][i], tm[k][i], S[i], r2[i]);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using IR = std::integral_constant<int, L - 2>;
+  if (tb.depth == 1) {
+    slots(I0{}, I1{});
+  } else if (tb.depth > 1) {
+    slots(I0{}, I2{});
+    if constexpr (L > 2)
+      if (tb.depth > 2) slots(I2{}, IR{});
+  }
+}
+
+// Workspace bounds: rows -P and P of G, whose targets min(tau, G xi_bar) add
+// clamp(p, lo, hi) - p to the position rows.
+template <int DIMS>
+__device__ __forceinline__ void box_push(const Box& box, const float p[DIMS], float S[DIMS], float& r2) {
+#pragma unroll
+  for (int x = 0; x < DIMS; ++x) {
+    const float e = fminf(fmaxf(p[x], box.lo[x]), box.hi[x]) - p[x];
+    S[x] += e;
+    r2 = fmaf(e, e, r2);
+  }
+}
+
+// Exchange between the MFMA column layout (lane: column cx of its sample, f4:
+// steps 4 q + 0..3) and the item layout (lane: items of its sample, one value
+// per axis), by DPP moves inside a quad; no LDS round trip.  quad_flip is the
+// 4 x 4 transpose across the quad's lanes and the four registers (its own
+// inverse): lane c, register r takes lane r's register c.
+template <int CTRL>
+__device__ __forceinline__ float dpp_any(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm [1,0,3,2], [2,3,0,1]
+
+// (the moves are arguments: inside a conditional they would run with the
+// source lanes switched off)
+__device__ __forceinline__ float pick(bool c, float x, float y) { return c ? x : y; }
+
+// 2D, 4 (or 8) slots per sample: axes in lanes 0 and 1 of the quad
+__device__ __forceinline__ void quad_items(f4 Y, int lane, float (&out)[1][2]) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const float a0 = pick(b1, dpp_any<kXor2>(Y[2]), Y[0]);
+  const float a1 = pick(b1, dpp_any<kXor2>(Y[3]), Y[1]);
+  out[0][0] = pick(b0, dpp_any<kXor1>(a1), a0);
+  out[0][1] = pick(b0, a1, dpp_any<kXor1>(a0));
+}
+__device__ __forceinline__ f4 quad_cols(const float (&d)[1][2], int lane) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const float a0 = pick(b0, dpp_any<kXor1>(d[0][1]), d[0][0]);
+  const float a1 = pick(b0, d[0][1], dpp_any<kXor1>(d[0][0]));
+  const float c0 = dpp_any<kXor2>(a0), c1 = dpp_any<kXor2>(a1);
+  return f4{pick(b1, 0.0f, a0), pick(b1, 0.0f, a1), pick(b1, 0.0f, c0), pick(b1, 0.0f, c1)};
+}
+// 3D
+__device__ __forceinline__ f4 quad_flip(f4 Y, int lane) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const float a0 = pick(b0, dpp_any<kXor1>(Y[1]), Y[0]);
+  const float a1 = pick(b0, Y[1], dpp_any<kXor1>(Y[0]));
+  const float a2 = pick(b0, dpp_any<kXor1>(Y[3]), Y[2]);
+  const float a3 = pick(b0, Y[3], dpp_any<kXor1>(Y[2]));
+  return f4{pick(b1, dpp_any<kXor2>(a2), a0), pick(b1, dpp_any<kXor2>(a3), a1),
+            pick(b1, a2, dpp_any<kXor2>(a0)), pick(b1, a3, dpp_any<kXor2>(a1))};
+}
+__device__ __forceinline__ void quad_items(f4 Y, int lane, float (&out)[1][3]) {
+  const f4 t = quad_flip(Y, lane);
+  out[0][0] = t[0];
+  out[0][1] = t[1];
+  out[0][2] = t[2];
+}
+__device__ __forceinline__ f4 quad_cols(const float (&d)[1][3], int lane) {
+  return quad_flip(f4{d[0][0], d[0][1], d[0][2], 0.0f}, lane);
+}
+// 2D, 2 slots per sample: lane cx holds the items of steps 4 q + 2 cx + 0, 1
+__device__ __forceinline__ void quad_items(f4 Y, int lane, float (&out)[2][2]) {
+  const bool b0 = lane & 1;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    out[i][0] = pick(b0, dpp_any<kXor1>(Y[2 + i]), Y[i]);
+    out[i][1] = pick(b0, Y[2 + i], dpp_any<kXor1>(Y[i]));
+  }
+}
+__device__ __forceinline__ f4 quad_cols(const float (&d)[2][2], int lane) {
+  const bool b0 = lane & 1;
+  f4 t;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    t[i] = pick(b0, dpp_any<kXor1>(d[i][1]), d[i][0]);
+    t[2 + i] = pick(b0, d[i][1], dpp_any<kXor1>(d[i][0]));
+  }
+  return t;
+}
+
+// Maximum of nonnegative values over the four 16-lane rows of a column, left in each of them:
+// swapping a register's copies across the rows leaves both sides in every lane.
+__device__ __forceinline__ float rows_max(float v) {
+  using u2 = __attribute__((ext_vector_type(2))) unsigned;
+  const unsigned u = __float_as_uint(v);
+  const u2 h = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(u, u, false, false));
+  const unsigned m = h.x > h.y ? h.x : h.y;
+  const u2 r = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(m, m, false, false));
+  return __uint_as_float(r.x > r.y ? r.x : r.y);
+}
+
+// x + sum_{e <= d} L[e] z[e], added in order; eight products' operands are
+// read before the first is added (entries past d are read, in range, and left
+// out of the sum).
+__device__ __forceinline__ float affine_row(float x, const float* L, const float* z, int d) {
+  for (int e0 = 0; e0 <= d; e0 += 8) {
+    float lv[8], zv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = min(e0 + u, d);
+      lv[u] = L[e];
+      zv[u] = z[e];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x = e0 + u <= d ? fmaf(lv[u], zv[u], x) : x;
+  }
+  return x;
 }
 
 // One block's work: whole projections of tiles first, first + stride, ...
@@ -808,76 +952,86 @@ __device__ __forceinline__ void item_push(const float4* rec, int M, const float 
 // [SPB*j, SPB*j + SPB) of problem t / blocks_per_problem, j its index within
 // the problem.  The problem constants (W rows, M11, Pi) are loaded once per
 // block.  AS: MFMA column slots per sample (4, or 2 in 2D); RT: 16-step time
-// blocks per wave; MAXT: the launch bound.
+// blocks per wave (wave w holds blocks w, w + TW, ... of the block's TW waves,
+// so that the crowded middle of the horizon is shared out); MAXT: the launch
+// bound; C3: there may be more than 12 coefficients per axis.
 template <int DIMS, int AS, int RT, int MAXT, bool BF16, bool LOOP, bool HIST = false,
-          bool TRAJ = false>
+          bool TRAJ = false, bool C3 = true>
 __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int stride, int total) {
   static_assert(AS == 4 || AS == 8 || (AS == 2 && DIMS == 2), "2 axis slots only hold 2D samples");
   constexpr int SPB = 16 / AS;           // samples per block
   // items per lane per time block; with 8 slots per sample only the lanes of
   // slots 0..3 carry an item (a wave holds 2 samples x 16 steps)
-  constexpr int IPR = AS <= 4 ? 4 / AS : 1;
-  constexpr int NI = RT * IPR;           // items per lane
+  constexpr int NI = AS <= 4 ? 4 / AS : 1;
   constexpr int MB = (MAXT / 64) * RT;   // 16-step block slots (power of two)
+  constexpr int NR = C3 ? 4 : 3;         // coefficient chunks
   extern __shared__ float4 sm4[];
   float* sm = reinterpret_cast<float*>(sm4);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, TW = blockDim.x >> 6;
   const int NB = TW * RT;
   const int nv = a.nv, K = a.K, M = a.M, D = DIMS * nv, D4 = round4(D);
   const Layout l = layout(DIMS, nv, M, NB, MB, SPB, a.mode);
-  {
-    // partial slots NB..MB-1 of both buffers stay zero (every reader passes
-    // the barrier after the first tile's staging first)
-    float* gz = sm + l.gp;
-    for (int i = tid; i < (MB - NB) * 256; i += blockDim.x) {
-      gz[NB * 256 + i] = 0.0f;
-      gz[(MB + NB) * 256 + i] = 0.0f;
-    }
-  }
+  // Partial right-hand sides: planes of 4 x 64 floats, one value per lane and
+  // coefficient chunk, so that only the chunks in use are read back.  In 2D
+  // with padding columns, a plane holds two blocks, the second in the lanes of
+  // the padding columns: half the LDS reads, which every wave of the block
+  // makes at the same time.  Slots NB..MB-1 of both buffers stay zero (every
+  // reader passes the barrier after the first tile's staging first).
+  constexpr bool HALF = DIMS == 2 && AS >= 4;
+  constexpr int NP = HALF ? MB / 2 : MB;
+  for (int i = tid; i < 2 * NP * 256; i += blockDim.x) sm[l.gp + i] = 0.0f;
   // MFMA column layout: q = row group, col = AS*cs + cx
   const int q = lane >> 4, col = lane & 15, cs = col / AS, cx = col % AS;
-  // items after the transpose: sample cs, step t0 + 16 rt + 4q + IPR cx + i
-  const int t0 = 16 * RT * w;
-  float tt[NI];
-  int t_item[NI];
-#pragma unroll
-  for (int n = 0; n < NI; ++n) {
-    t_item[n] = t0 + 16 * (n / IPR) + 4 * q + IPR * cx + (n % IPR);
-    tt[n] = a.dt * static_cast<float>(t_item[n]);
-  }
-  // time window of each row of 16 lanes: steps t0 + 16 rt + 4 q + 0..3
-  float tmid[4], thalf[4];
-#pragma unroll
-  for (int qq = 0; qq < 4; ++qq) {
-    thalf[qq] = a.dt * (8.0f * (RT - 1) + 1.5f);
-    tmid[qq] = a.dt * (static_cast<float>(t0 + 4 * qq) + 8.0f * (RT - 1) + 1.5f);
-  }
 
+  TimeBlock<NI, DIMS> blk[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int t0 = 16 * (w + TW * rt);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      // items after the transpose: sample cs, step t0 + 4 q + NI cx + i
+      blk[rt].t[i] = t0 + 4 * q + NI * cx + i;
+      blk[rt].tt[i] = a.dt * static_cast<float>(blk[rt].t[i]);
+    }
+    // time window of each row of 16 lanes: steps t0 + 4 q + 0..3
+#pragma unroll
+    for (int qq = 0; qq < 4; ++qq)
+      blk[rt].tmid[qq] = a.dt * (static_cast<float>(t0 + 4 * qq) + 1.5f);
+  }
   float4* rec = reinterpret_cast<float4*>(sm + l.rec);
   float* xs = sm + l.xs;
 
   // ---- per-lane MFMA operands and sample state -------------------------------
-  float Af[RT][3][4], Ab[RT][3][4], Am[4], Ap[4];
+  // (loads from clamped places, padded afterwards: a load under a condition
+  // becomes a branch and a memory round trip of its own)
+  float Af[RT][3][4], Ab[RT][3][4], Am[4];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int d = 0; d < 3; ++d)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int tf = t0 + 16 * rt + col, cf = coef_of(q, r);
-        Af[rt][d][r] = (tf < K && cf < nv) ? a.W[(tf * 3 + d) * nv + cf] : 0.0f;
-        const int tb = t0 + 16 * rt + 4 * q + r, cb = coef_of(col >> 2, col & 3);
-        Ab[rt][d][r] = (tb < K && cb < nv) ? a.W[(tb * 3 + d) * nv + cb] : 0.0f;
+        const int t0 = 16 * (w + TW * rt);
+        const int tf = t0 + col, cf = coef_of(q, r);
+        const float wf = a.W[(min(tf, K - 1) * 3 + d) * nv + min(cf, nv - 1)];
+        Af[rt][d][r] = (tf < K && cf < nv) ? wf : 0.0f;
+        const int tb = t0 + 4 * q + r, cb = coef_of(col >> 2, col & 3);
+        const float wb = a.W[(min(tb, K - 1) * 3 + d) * nv + min(cb, nv - 1)];
+        Ab[rt][d][r] = (tb < K && cb < nv) ? wb : 0.0f;
       }
+  // (Pi and c0 = M12 b enter the first iteration only: they wait in LDS)
+  float* first_op = sm + l.first + lane * 4;
   const int crow = coef_of(col >> 2, col & 3);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int ck = coef_of(q, r);
     const bool ok = (crow < nv) && (ck < nv);
-    Am[r] = ok ? a.M11[crow * nv + ck] : 0.0f;
-    Ap[r] = ok ? a.Pi[crow * nv + ck] : 0.0f;
+    const int at = min(crow, nv - 1) * nv + min(ck, nv - 1);
+    const float m = a.M11[at], pi = a.Pi[at];
+    Am[r] = ok ? m : 0.0f;
+    if (w == 0) first_op[r] = ok ? pi : 0.0f;
   }
-  const bool chunk3 = nv > 12;  // slot r = 3 holds coefficients 12..15
+  const bool chunk3 = C3 && nv > 12;  // slot r = 3 holds coefficients 12..15
   const float rho = a.rho;
   f4 xb;
   // mixed precision: W^T rows as BF16, M11 as a BF16 hi/lo pair
@@ -892,47 +1046,29 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
     Mlo = pack_bf16(Am[0] - from_bf16(Mhi[0]), Am[1] - from_bf16(Mhi[1]),
                     Am[2] - from_bf16(Mhi[2]), Am[3] - from_bf16(Mhi[3]));
   }
-  float* xt = sm + l.xt + w * RT * kXtBlock;
-  uint32_t* wm = reinterpret_cast<uint32_t*>(sm + l.cm) + w * 4 * ((M + 63) / 64);
+  const int mask_words = 4 * ((M + 63) / 64);
+  uint32_t* wm0 = reinterpret_cast<uint32_t*>(sm + l.cm) + w * RT * mask_words;
 
-  // Forward rows of this wave's time blocks, transposed to the item layout.
-  auto forward = [&](float p[NI][DIMS], float v[NI][DIMS], float ac[NI][DIMS]) {
-    const f4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      // one accumulation chain per row type over k-chunks 0, 1, 2[, 3]; the
-      // three chains interleave, so each product waits on nothing
-      f4 Y0 = mfma(Af[rt][0][0], xb[0], z), Y1 = mfma(Af[rt][1][0], xb[0], z),
-         Y2 = mfma(Af[rt][2][0], xb[0], z);
-#pragma unroll
-      for (int c = 1; c < 3; ++c) {
-        Y0 = mfma(Af[rt][0][c], xb[c], Y0);
-        Y1 = mfma(Af[rt][1][c], xb[c], Y1);
-        Y2 = mfma(Af[rt][2][c], xb[c], Y2);
-      }
-      if (chunk3) {
-        Y0 = mfma(Af[rt][0][3], xb[3], Y0);
-        Y1 = mfma(Af[rt][1][3], xb[3], Y1);
-        Y2 = mfma(Af[rt][2][3], xb[3], Y2);
-      }
-      float* x0 = xt + rt * kXtBlock + xt_at(lane);
-      *reinterpret_cast<f4*>(x0) = Y0;
-      *reinterpret_cast<f4*>(x0 + kXtRow) = Y1;
-      *reinterpret_cast<f4*>(x0 + 2 * kXtRow) = Y2;
+  // Forward rows of row type d of a time block: one accumulation chain over
+  // the k-chunks, in the column layout.
+  auto chain = [&](int rt, int d) {
+    f4 Y = mfma(Af[rt][d][0], xb[0], f4{0.0f, 0.0f, 0.0f, 0.0f});
+    Y = mfma(Af[rt][d][1], xb[1], Y);
+    Y = mfma(Af[rt][d][2], xb[2], Y);
+    if (chunk3) Y = mfma(Af[rt][d][3], xb[3], Y);
+    return Y;
+  };
+  // maximum of a nonnegative value over a sample's columns and coefficient
+  // rows, in every lane that carries an item of the sample (NaN above +inf)
+  auto quad_max = [&](float v) {
+    uint32_t u = __float_as_uint(v);
+    const uint32_t o1 = __float_as_uint(dpp_any<kXor1>(__uint_as_float(u)));
+    u = u > o1 ? u : o1;
+    if constexpr (AS > 2) {
+      const uint32_t o2 = __float_as_uint(dpp_any<kXor2>(__uint_as_float(u)));
+      u = u > o2 ? u : o2;
     }
-    wave_lds_sync();
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int i = 0; i < IPR; ++i)
-#pragma unroll
-        for (int x = 0; x < DIMS; ++x) {
-          const int src = rt * kXtBlock + xt_at(lane - cx + x) + IPR * cx + i;
-          p[rt * IPR + i][x] = xt[src];
-          v[rt * IPR + i][x] = xt[kXtRow + src];
-          ac[rt * IPR + i][x] = xt[2 * kXtRow + src];
-        }
-    wave_lds_sync();
+    return rows_max(__uint_as_float(u));
   };
 
   int cur_prob = -1;
@@ -940,15 +1076,12 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
     const int prob = t / a.blocks_per_problem;
     const int s0 = (t - prob * a.blocks_per_problem) * SPB;
     const int ns = min(SPB, a.N - s0);
-    bool item_ok[NI];
-#pragma unroll
-    for (int n = 0; n < NI; ++n) item_ok[n] = (t_item[n] < K) && (cs < ns) && (AS <= 4 || cx < 4);
+    const float* bc = a.bc + prob * a.bc_stride;
     // ---- scene records, samples ---------------------------------------------
     // (every reader of the previous tile's records passed the barrier that
     // precedes its epilogue)
     if (prob != cur_prob)
       build_records<DIMS, TRAJ>(a.obs + prob * a.obs_stride, M, tid, blockDim.x, rec, K);
-    const float* opath = a.obs + prob * a.obs_stride;
     cur_prob = prob;
     if (a.mode == kFromInput) {
       const float* src = a.xi_in + prob * a.xi_in_stride + static_cast<int64_t>(s0) * D;
@@ -978,11 +1111,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       __syncthreads();
       for (int i = tid; i < ns * D; i += blockDim.x) {
         const int s = i / D, d = i - s * D;
-        const float* zz = sZ + s * D4;
-        const float* Lr = sL + d * D;
-        float x = sMu[d];
-        for (int e = 0; e <= d; ++e) x = fmaf(Lr[e], zz[e], x);
-        xs[s * D4 + d] = x;
+        xs[s * D4 + d] = affine_row(sMu[d], sL + d * D, sZ + s * D4, d);
       }
       __syncthreads();
       if (a.xi_src) {
@@ -990,31 +1119,72 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
         for (int i = tid; i < ns * D; i += blockDim.x) dst[i] = xs[(i / D) * D4 + i % D];
       }
     }
+    if (w == 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = coef_of(q, r);
+        float s = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+          s = fmaf(a.M12[min(c, nv - 1) * 6 + i], bc[min(cx, DIMS - 1) * 6 + i], s);
+        first_op[256 + r] = (cx < DIMS && cs < ns && c < nv) ? s : 0.0f;
+      }
+    }
     __syncthreads();
 
     const bool colok = (cx < DIMS) && (cs < ns);
-    const float* bc = a.bc + prob * a.bc_stride;
-    f4 xi, c0v;
-  #pragma unroll
+    f4 xi;
+#pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int c = coef_of(q, r);
-      const bool ok = colok && (c < nv);
-      xi[r] = ok ? xs[cs * D4 + cx * nv + c] : 0.0f;
-      float s = 0.0f;
-      if (ok)
-        for (int i = 0; i < 6; ++i) s = fmaf(a.M12[c * 6 + i], bc[cx * 6 + i], s);
-      c0v[r] = s;
+      xi[r] = (colok && (c < nv)) ? xs[cs * D4 + cx * nv + c] : 0.0f;
     }
     xb = xi;
     f4 lam = {0.0f, 0.0f, 0.0f, 0.0f};
-    CullCache<NI, DIMS> cull;
-    cull.valid = false;
-    cull.pairs = 0;
-    cull.nok = 0;
-#pragma unroll
-    for (int n = 0; n < NI; ++n) cull.nok += static_cast<uint32_t>(__builtin_popcountll(__ballot(item_ok[n])));
-
+    Scene sc{rec, a.obs + prob * a.obs_stride, M, K, 0.0f, a.dt * 1.5f};
     {
+      float cmin = INFINITY;
+      for (int j = lane; j < M; j += 64) cmin = fminf(cmin, rec[j].w);
+      sc.unit = kSlack * wave_min(cmin);
+    }
+    uint32_t pairs = 0;
+    // Budgets (per lane, in units of max|Delta xi_bar| of the lane's sample):
+    // how far the coefficients may still move before the positions of the
+    // lane's items can come near an obstacle (Bp), or their |v|, |a| can
+    // exceed the bounds (Bv, Ba), see the whole-horizon shape below.  While
+    // every lane of the wave has budget left, that row type's push-outs are
+    // exactly zero and its rows are not evaluated.
+    float Bp[RT], Bv[RT], Ba[RT], X;
+    bool needP[RT], needV[RT], needA[RT], any_ok[RT];
+    {
+      float m = 0.0f;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) m = fmaxf(m, fabsf(xi[r]));
+      X = quad_max(m) * 1.000002f;
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      TimeBlock<NI, DIMS>& b = blk[rt];
+      b.nok = 0;
+      b.npairs = 0;
+      b.depth = 0;
+      any_ok[rt] = false;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        b.ok[i] = (b.t[i] < K) && (cs < ns) && (AS <= 4 || cx < 4);
+        b.nok += static_cast<uint32_t>(__builtin_popcountll(__ballot(b.ok[i])));
+        any_ok[rt] = any_ok[rt] || b.ok[i];
+        b.lim[i] = -1.0f;
+#pragma unroll
+        for (int x = 0; x < DIMS; ++x) b.pref[i][x] = 0.0f;
+      }
+      Bp[rt] = Bv[rt] = Ba[rt] = -1.0f;
+      needP[rt] = needV[rt] = needA[rt] = true;
+    }
+    const float pscale = a.bscale[0] * (DIMS == 3 ? 0.57735026f : 0.70710678f);
+    auto budget = [&](float m) { return fmaf(m, 0.99899f, -1.0e-5f * X); };
+
+    if constexpr (RT == 1) {
       // waves of mid-trajectory time blocks carry the most obstacle
       // candidates (the samples spread most there) and set the pace at every
       // barrier: they get issue priority over the wave that shares their SIMD
@@ -1026,93 +1196,159 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       else if (pr == 1) __builtin_amdgcn_s_setprio(1);
       else __builtin_amdgcn_s_setprio(0);
     }
+    // (the position rows are evaluated as soon as an iterate is there, beside
+    // the reductions of its budgets)
+    f4 YP[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) YP[rt] = chain(rt, 0);
+    // bit 2 rt + b: this block's partials in buffer b may be other than zero
+    uint32_t dirty = ~0u;
     // ---- projection iterations ---------------------------------------------------
-    for (int k = 0; k < a.n_iter; ++k) {
-      float p[NI][DIMS], v[NI][DIMS], ac[NI][DIMS];
-      forward(p, v, ac);
-      float S[NI][DIMS], dv[NI][DIMS], da[NI][DIMS], r2[NI];
-      item_push<DIMS, false, NI, HIST, TRAJ>(rec, M, tt, tmid, thalf, item_ok, p, v, ac, a.vmax, a.amax,
-                                             a.box, S, dv, da, r2, lane, cull, wm, opath, t_item, K);
-      if constexpr (HIST) {
-        // squared push-outs of this iteration per (t, sample), summed per
-        // sample after the barrier below (double-buffered by iteration)
-        float* hb = sm + l.hist + (k & 1) * 16 * NB * SPB;
-  #pragma unroll
-        for (int n = 0; n < NI; ++n)
-          if (AS <= 4 || cx < 4) hb[t_item[n] * SPB + cs] = item_ok[n] ? r2[n] : 0.0f;
-      }
-      // back to the column layout: slot AS*i + x of the lane's f4 holds axis x
-      // of item i
-  #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        f4 T0 = {0.0f, 0.0f, 0.0f, 0.0f}, T1 = T0, T2 = T0;
-  #pragma unroll
-        for (int i = 0; i < IPR; ++i)
-  #pragma unroll
-          for (int x = 0; x < DIMS; ++x) {
-            T0[AS * i + x] = S[rt * IPR + i][x];
-            T1[AS * i + x] = dv[rt * IPR + i][x];
-            T2[AS * i + x] = da[rt * IPR + i][x];
-          }
-        float* x0 = xt + rt * kXtBlock + xt_at(lane);
-        *reinterpret_cast<f4*>(x0) = T0;
-        *reinterpret_cast<f4*>(x0 + kXtRow) = T1;
-        *reinterpret_cast<f4*>(x0 + 2 * kXtRow) = T2;
-      }
-      wave_lds_sync();
-      float B[RT][3][4];
-  #pragma unroll
+    for (int k = 0;; ++k) {
+      // positions, and the obstacle search where they have left the reach of
+      // the last one (one more time after the last iteration, for the residual)
+      const bool last = k == a.n_iter;
+      float p[RT][NI][DIMS];
+#pragma unroll
       for (int rt = 0; rt < RT; ++rt)
-  #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int src = rt * kXtBlock + xt_at(lane - cx + r / IPR) + AS * (r % IPR) + cx;
-          // (8 slots: columns 4..7 of a sample are padding and stay zero)
-          const bool pad = (AS == 8) && (cx >= 4);
-          B[rt][0][r] = pad ? 0.0f : xt[src];
-          B[rt][1][r] = pad ? 0.0f : xt[kXtRow + src];
-          B[rt][2][r] = pad ? 0.0f : xt[2 * kXtRow + src];
+        if (needP[rt] || last) {
+          quad_items(YP[rt], lane, p[rt]);
+          if (__builtin_expect(!still_valid<DIMS>(blk[rt], p[rt]), 0))
+            search_obstacles<DIMS, TRAJ>(sc, blk[rt], p[rt], lane, wm0 + rt * mask_words,
+                                         a.pair_count != nullptr);
         }
+      if (last) break;
       const f4 zb = {0.0f, 0.0f, 0.0f, 0.0f};
       const bool lowp = BF16 && (k < a.bf16_iters);
-      float* gp = sm + l.gp + (k & 1) * MB * 256;
-      if (lowp) {
-        // right-hand side with BF16 operands, FP32 accumulation: one K = 16
-        // MFMA per row type covers a whole 16-step block
-  #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          f4 g = zb;
-  #pragma unroll
-          for (int d = 0; d < 3; ++d)
-            g = mfma_bf16(Abf[rt][d], pack_bf16(B[rt][d][0], B[rt][d][1], B[rt][d][2], B[rt][d][3]), g);
-          *reinterpret_cast<f4*>(gp + (w * RT + rt) * 256 + lane * 4) = g;
+      float* gp = sm + l.gp + (k & 1) * NP * 256;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        TimeBlock<NI, DIMS>& b = blk[rt];
+        // push-outs of the row types that may push; nz: those with a nonzero
+        // push-out on some item of the block (the others are left out of the
+        // right-hand side: adding exact zeros to an accumulator that starts
+        // at +0 changes nothing)
+        uint32_t nz = 0;
+        float S[NI][DIMS], dv[NI][DIMS], da[NI][DIMS], r2[NI];
+#pragma unroll
+        for (int n = 0; n < NI; ++n) r2[n] = 0.0f;
+        f4 YV, YA;
+        if (needV[rt]) YV = chain(rt, 1);
+        if (needA[rt]) YA = chain(rt, 2);
+        if (needP[rt]) {
+#pragma unroll
+          for (int n = 0; n < NI; ++n)
+#pragma unroll
+            for (int x = 0; x < DIMS; ++x) S[n][x] = 0.0f;
+          obstacle_pushes<DIMS, false, HIST, TRAJ>(sc, b, p[rt], S, r2, lane, wm0 + rt * mask_words);
+          pairs += b.npairs;
+          if (a.box.on) {
+#pragma unroll
+            for (int n = 0; n < NI; ++n)
+              if (b.ok[n]) box_push<DIMS>(a.box, p[rt][n], S[n], r2[n]);
+          } else if (b.depth == 0) {
+            float left = INFINITY;
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {
+              float d2 = 0.0f;
+#pragma unroll
+              for (int x = 0; x < DIMS; ++x) {
+                const float e = p[rt][n][x] - b.pref[n][x];
+                d2 = fmaf(e, e, d2);
+              }
+              left = b.ok[n] ? fminf(left, b.lim[n] - __builtin_amdgcn_sqrtf(d2) * 1.000001f) : left;
+            }
+            Bp[rt] = any_ok[rt] ? budget(left * pscale) : INFINITY;
+          }
+          bool any = false;
+#pragma unroll
+          for (int n = 0; n < NI; ++n)
+#pragma unroll
+            for (int x = 0; x < DIMS; ++x) any = any || (S[n][x] != 0.0f);
+          nz = __ballot(any) != 0ull ? 1u : 0u;
         }
-      } else {
-        f4 G[RT];
-  #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          // two accumulation chains over the three row types and four
-          // k-chunks, added once at the end: one chain is faster for a lone
-          // small launch, but its dependent products stall full launches
-          // (N = 64000: 8.2 against 6.0 ms)
-          constexpr int NCH = 2;
-          f4 acc[NCH];
-  #pragma unroll
-          for (int c = 0; c < NCH; ++c) acc[c] = zb;
-  #pragma unroll
-          for (int d = 0; d < 3; ++d)
-  #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[(4 * d + r) % NCH] = mfma(Ab[rt][d][r], B[rt][d][r], acc[(4 * d + r) % NCH]);
-          f4 gs = acc[0];
-  #pragma unroll
-          for (int c = 1; c < NCH; ++c) gs = gs + acc[c];
-          G[rt] = gs;
+        // velocity / acceleration bounds
+        auto bounds = [&](const f4& Y, float wmax, float scale, float (&d)[NI][DIMS], float& B,
+                          uint32_t bit) {
+          float wv[NI][DIMS];
+          quad_items(Y, lane, wv);
+          float m = 0.0f;
+          bool over = false;
+          const float wcap = fminf(wmax * wmax, 3.402823466e38f);  // (an infinite |w|^2 is over any bound)
+#pragma unroll
+          for (int n = 0; n < NI; ++n) {
+            float ww = 0.0f;
+#pragma unroll
+            for (int x = 0; x < DIMS; ++x) ww = fmaf(wv[n][x], wv[n][x], ww);
+            over = over || (b.ok[n] && !(ww <= wcap));
+            m = b.ok[n] ? fmaxf(m, ww) : m;
+          }
+          if (__ballot(over) != 0ull) {
+            nz |= bit;
+            B = -1.0f;
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {
+#pragma unroll
+              for (int x = 0; x < DIMS; ++x) d[n][x] = 0.0f;
+              if (b.ok[n]) bound_push<DIMS>(wv[n], wmax, d[n], r2[n]);
+            }
+          } else {
+            // (v_sqrt_f32 is within 1 ulp)
+            B = any_ok[rt] ? budget((wmax * 0.999999f - __builtin_amdgcn_sqrtf(m) * 1.000001f) * scale)
+                           : INFINITY;
+          }
+        };
+        if (needV[rt]) bounds(YV, a.vmax, a.bscale[1], dv, Bv[rt], 2u);
+        if (needA[rt]) bounds(YA, a.amax, a.bscale[2], da, Ba[rt], 4u);
+        if constexpr (HIST) {
+          // squared push-outs of this iteration per (t, sample), summed per
+          // sample after the barrier below (double-buffered by iteration)
+          float* hb = sm + l.hist + (k & 1) * 16 * NB * SPB;
+#pragma unroll
+          for (int n = 0; n < NI; ++n)
+            if (AS <= 4 || cx < 4) hb[b.t[n] * SPB + cs] = b.ok[n] ? r2[n] : 0.0f;
         }
-        // issue the LDS reads before the MFMAs that consume them
-        __builtin_amdgcn_sched_group_barrier(0x100, 12 * RT, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 12 * RT, 0);
-  #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          *reinterpret_cast<f4*>(gp + (w * RT + rt) * 256 + lane * 4) = G[rt];
+        // right-hand side of this block
+        const uint32_t db = 1u << (2 * rt + (k & 1));
+        if (nz || (dirty & db)) {
+          f4 part;
+          if (lowp) {
+            // BF16 operands, FP32 accumulation: one K = 16 MFMA per row type
+            // covers a whole 16-step block
+            part = zb;
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+              if (nz & (1u << d)) {
+                const f4 B = quad_cols(d == 0 ? S : d == 1 ? dv : da, lane);
+                part = mfma_bf16(Abf[rt][d], pack_bf16(B[0], B[1], B[2], B[3]), part);
+              }
+          } else {
+            // two accumulation chains over the three row types and four
+            // k-chunks, added once at the end: one chain is faster for a lone
+            // small launch, but its dependent products stall full launches
+            // (N = 64000: 8.2 against 6.0 ms)
+            f4 acc0 = zb, acc1 = zb;
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+              if (nz & (1u << d)) {
+                const f4 B = quad_cols(d == 0 ? S : d == 1 ? dv : da, lane);
+                acc0 = mfma(Ab[rt][d][0], B[0], acc0);
+                acc1 = mfma(Ab[rt][d][1], B[1], acc1);
+                acc0 = mfma(Ab[rt][d][2], B[2], acc0);
+                acc1 = mfma(Ab[rt][d][3], B[3], acc1);
+              }
+            part = acc0 + acc1;
+          }
+          const int tb = w + TW * rt;
+          float* slot = gp + (HALF && tb >= NP ? tb - NP : tb) * 256 + lane + (HALF && tb >= NP ? 2 : 0);
+          if (!HALF || !(lane & 2)) {
+            slot[0] = part[0];
+            slot[64] = part[1];
+            slot[128] = part[2];
+            if (chunk3) slot[192] = part[3];
+          }
+          dirty = (dirty & ~db) | (nz ? db : 0u);
+        }
       }
       __syncthreads();
       // g = +0 + the block partials added one by one in time-block order
@@ -1121,8 +1357,49 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       // partial of exact zeros leaves the sum as it is: the whole-horizon
       // shape adds only its nonzero partials and gets the same bits.
       f4 g = {0.0f, 0.0f, 0.0f, 0.0f};
-  #pragma unroll
-      for (int b = 0; b < MB; ++b) g = g + *reinterpret_cast<const f4*>(gp + b * 256 + lane * 4);
+      auto sum_chunks = [&](auto n_tag, int r0) {
+        constexpr int N = decltype(n_tag)::value;
+        float v[NP <= 8 ? NP : 4][N], t[N];
+        if constexpr (NP <= 8) {
+#pragma unroll
+          for (int b = 0; b < NP; ++b)
+#pragma unroll
+            for (int r = 0; r < N; ++r) v[b][r] = gp[b * 256 + 64 * (r0 + r) + lane];
+#pragma unroll
+          for (int r = 0; r < N; ++r) t[r] = v[0][r];
+#pragma unroll
+          for (int b = 1; b < NP; ++b)
+#pragma unroll
+            for (int r = 0; r < N; ++r) t[r] += v[b][r];
+        } else {
+          // (more than eight planes: four at a time, as far as there are blocks)
+#pragma unroll
+          for (int r = 0; r < N; ++r) t[r] = 0.0f;
+          for (int b0 = 0; b0 < NB; b0 += 4) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+              for (int r = 0; r < N; ++r) v[b][r] = gp[(b0 + b) * 256 + 64 * (r0 + r) + lane];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+              for (int r = 0; r < N; ++r) t[r] += v[b][r];
+          }
+        }
+        if constexpr (HALF) {
+          // (the second half of the blocks, from the padding columns' lanes)
+#pragma unroll
+          for (int b = 0; b < NP; ++b)
+#pragma unroll
+            for (int r = 0; r < N; ++r) t[r] += dpp_any<kXor2>(v[b][r]);
+#pragma unroll
+          for (int r = 0; r < N; ++r) t[r] = (lane & 2) ? 0.0f : t[r];
+        }
+#pragma unroll
+        for (int r = 0; r < N; ++r) g[r0 + r] = t[r];
+      };
+      sum_chunks(std::integral_constant<int, 3>{}, 0);
+      if (chunk3) sum_chunks(std::integral_constant<int, 1>{}, 3);
       if constexpr (HIST) {
         // ||F xi_bar^k - e^{k+1}|| per sample, summed over t in order
         if (tid < ns) {
@@ -1132,14 +1409,17 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
           a.resid_hist[static_cast<int64_t>(k) * a.N + s0 + tid] = sqrtf(h);
         }
       }
-      lam += rho * g;
-      const f4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int r = 0; r < NR; ++r) lam[r] += rho * g[r];
+      const f4 xold = xb;
       if (k == 0) {
+        const f4 Ap = *reinterpret_cast<const f4*>(first_op);
+        const f4 c0v = *reinterpret_cast<const f4*>(first_op + 256);
         const f4 u = lam + rho * g;
         const f4 h0 = mfma(Ap[1], xi[1], mfma(Ap[0], xi[0], c0v));
-        f4 h1 = mfma(Ap[2], xi[2], z);
-        const f4 h2 = mfma(Am[1], u[1], mfma(Am[0], u[0], z));
-        f4 h3 = mfma(Am[2], u[2], z);
+        f4 h1 = mfma(Ap[2], xi[2], zb);
+        const f4 h2 = mfma(Am[1], u[1], mfma(Am[0], u[0], zb));
+        f4 h3 = mfma(Am[2], u[2], zb);
         if (chunk3) {
           h1 = mfma(Ap[3], xi[3], h1);
           h3 = mfma(Am[3], u[3], h3);
@@ -1153,22 +1433,37 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
                                 u[2] - from_bf16(uh[2]), u[3] - from_bf16(uh[3]));
         // (the two small cross terms first, then the leading one, all into
         // one accumulator)
-        xb = xb + mfma_bf16(Mhi, uh, mfma_bf16(Mlo, uh, mfma_bf16(Mhi, ul, z)));
+        xb = xb + mfma_bf16(Mhi, uh, mfma_bf16(Mlo, uh, mfma_bf16(Mhi, ul, zb)));
       } else {
         // accumulated straight into xi_bar: one chain, no VALU sums
-        const f4 u = (xi - xb) + lam + rho * g;
+        float u[4];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) u[r] = (xi[r] - xb[r]) + lam[r] + rho * g[r];
         xb = mfma(Am[2], u[2], mfma(Am[1], u[1], mfma(Am[0], u[0], xb)));
         if (chunk3) xb = mfma(Am[3], u[3], xb);
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) YP[rt] = chain(rt, 0);
+      // the budgets of a sample shrink by its largest coefficient change
+      // (rounded up)
+      float m = 0.0f;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) m = fmaxf(m, fabsf(xb[r] - xold[r]));
+      const float dl = quad_max(m) * 1.000002f;
+      X += dl;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        Bp[rt] -= dl;
+        Bv[rt] -= dl;
+        Ba[rt] -= dl;
+        needP[rt] = __ballot(!(Bp[rt] >= 0.0f)) != 0ull;
+        needV[rt] = __ballot(!(Bv[rt] >= 0.0f)) != 0ull;
+        needA[rt] = __ballot(!(Ba[rt] >= 0.0f)) != 0ull;
       }
     }
 
     // ---- residual and smoothness cost of the returned iterate -----------------------
     {
-      float p[NI][DIMS], v[NI][DIMS], ac[NI][DIMS];
-      forward(p, v, ac);
-      float S[NI][DIMS], dv[NI][DIMS], da[NI][DIMS], r2[NI];
-      item_push<DIMS, true, NI, false, TRAJ>(rec, M, tt, tmid, thalf, item_ok, p, v, ac, a.vmax, a.amax,
-                                             a.box, S, dv, da, r2, lane, cull, wm, opath, t_item, K);
       float* fin = sm + l.fin;
       // segment of the path-following term: start p0 -> goal pf of this problem
       float sg[DIMS], ug[DIMS], iuu = 0.0f;
@@ -1182,19 +1477,41 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
         }
         iuu = uu > 0.0f ? 1.0f / uu : 0.0f;
       }
-  #pragma unroll
-      for (int n = 0; n < NI; ++n) {
-        float cc = 0.0f;
-        if (a.cost.kind == 0) {
-  #pragma unroll
-          for (int x = 0; x < DIMS; ++x) cc = fmaf(ac[n][x], ac[n][x], cc);
-        } else {
-          cc = weighted_cost<DIMS>(p[n], v[n], ac[n], a.cost, sg, ug, iuu);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const TimeBlock<NI, DIMS>& b = blk[rt];
+        float p[NI][DIMS], v[NI][DIMS], ac[NI][DIMS], S[NI][DIMS], r2[NI];
+        quad_items(YP[rt], lane, p);
+        quad_items(chain(rt, 1), lane, v);
+        quad_items(chain(rt, 2), lane, ac);
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+          r2[n] = 0.0f;
+#pragma unroll
+          for (int x = 0; x < DIMS; ++x) S[n][x] = 0.0f;
         }
-        float* f = fin + 2 * (t_item[n] * SPB + cs);
-        if (AS <= 4 || cx < 4) {  // lanes without items own no slot
-          f[0] = item_ok[n] ? r2[n] : 0.0f;
-          f[1] = item_ok[n] ? cc : 0.0f;
+        obstacle_pushes<DIMS, true, true, TRAJ>(sc, b, p, S, r2, lane, wm0 + rt * mask_words);
+        pairs += b.npairs;
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+          float cc = 0.0f;
+          if (b.ok[n]) {
+            float d[DIMS];
+            bound_push<DIMS>(v[n], a.vmax, d, r2[n]);
+            bound_push<DIMS>(ac[n], a.amax, d, r2[n]);
+            if (a.box.on) box_push<DIMS>(a.box, p[n], S[n], r2[n]);
+          }
+          if (a.cost.kind == 0) {
+#pragma unroll
+            for (int x = 0; x < DIMS; ++x) cc = fmaf(ac[n][x], ac[n][x], cc);
+          } else {
+            cc = weighted_cost<DIMS>(p[n], v[n], ac[n], a.cost, sg, ug, iuu);
+          }
+          float* f = fin + 2 * (b.t[n] * SPB + cs);
+          if (AS <= 4 || cx < 4) {  // lanes without items own no slot
+            f[0] = b.ok[n] ? r2[n] : 0.0f;
+            f[1] = b.ok[n] ? cc : 0.0f;
+          }
         }
       }
     }
@@ -1202,10 +1519,18 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
     if (tid < ns) {
       const int s = tid;
       float r2 = 0.0f, cc = 0.0f;
-      for (int t = 0; t < K; ++t) {
-        const float* f = sm + l.fin + 2 * (t * SPB + s);
-        r2 += f[0];
-        cc += f[1];
+      // (16 steps' reads in flight; the slots past the horizon hold zeros, and
+      // neither sum is ever -0)
+      for (int t = 0; t < K; t += 16) {
+        float2 f[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          f[u] = *reinterpret_cast<const float2*>(sm + l.fin + 2 * ((t + u) * SPB + s));
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          r2 += f[u].x;
+          cc += f[u].y;
+        }
       }
       const float r = sqrtf(r2);
       const int64_t nb = prob * a.n_stride + s0 + s;
@@ -1215,7 +1540,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       if (a.resid2) a.resid2[dense] = r;
       if (a.c12) a.c12[dense] = cc;
     }
-    if (a.pair_count && lane == 0) atomicAdd(a.pair_count, static_cast<unsigned long long>(cull.pairs));
+    if (a.pair_count && lane == 0) atomicAdd(a.pair_count, static_cast<unsigned long long>(pairs));
     if (w == 0 && colok) {
       float* dst = a.xi_out + prob * a.xi_out_stride + static_cast<int64_t>(s0 + cs) * D + cx * nv;
       float* dst2 = a.xi_out2 ? a.xi_out2 + (static_cast<int64_t>(prob) * a.N + s0 + cs) * D + cx * nv
@@ -1243,26 +1568,26 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
 // logical block ids are laid out so that each XCD (which receives every 8th
 // hardware block) walks a contiguous range of tiles, keeping a problem's
 // scene in one L2.
-template <int DIMS, int AS, int RT, int MAXT, bool BF16, bool LOOP>
-__global__ __launch_bounds__(MAXT) void project_kernel(ProjArgs a, int total) {
+template <int DIMS, int AS, int RT, int MAXT, bool BF16, bool LOOP, bool C3 = true>
+__global__ __launch_bounds__(MAXT, RT == 1 ? 4 : 2) void project_kernel(ProjArgs a, int total) {
   const int G = gridDim.x;
   int lb = blockIdx.x;
   if ((G & 7) == 0) lb = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
-  project_block<DIMS, AS, RT, MAXT, BF16, LOOP>(a, lb, G, total);
+  project_block<DIMS, AS, RT, MAXT, BF16, LOOP, false, false, C3>(a, lb, G, total);
 }
 
 // The default shape with the per-iteration residual history (HIST, one
 // problem) and/or obstacles given by their paths (TRAJ); one block per tile.
-template <int DIMS, int MAXT, bool BF16, bool HIST, bool TRAJ>
-__global__ __launch_bounds__(MAXT) void project_special_kernel(ProjArgs a, int total) {
-  project_block<DIMS, 4, 1, MAXT, BF16, false, HIST, TRAJ>(a, blockIdx.x, 1, total);
+template <int DIMS, int MAXT, bool BF16, bool HIST, bool TRAJ, bool C3 = true>
+__global__ __launch_bounds__(MAXT, 4) void project_special_kernel(ProjArgs a, int total) {
+  project_block<DIMS, 4, 1, MAXT, BF16, false, HIST, TRAJ, C3>(a, blockIdx.x, 1, total);
 }
 
 // Descriptor table (heterogeneous requests sharing n_steps): task t owns
 // blocks [prefix[t], prefix[t+1]); every field of its ProjArgs is its own.
 // Serving uses the default tile shape (4 axis slots, one time block per wave).
-template <int DIMS, int MAXT, bool BF16>
-__global__ __launch_bounds__(MAXT) void project_task_kernel(const ProjArgs* tasks,
+template <int DIMS, int MAXT, bool BF16, bool C3 = true>
+__global__ __launch_bounds__(MAXT, 4) void project_task_kernel(const ProjArgs* tasks,
                                                             const int* prefix, int n_tasks) {
   int lo = 0, hi = n_tasks;
   while (hi - lo > 1) {
@@ -1270,8 +1595,8 @@ __global__ __launch_bounds__(MAXT) void project_task_kernel(const ProjArgs* task
     if (prefix[mid] <= static_cast<int>(blockIdx.x)) lo = mid;
     else hi = mid;
   }
-  project_block<DIMS, 4, 1, MAXT, BF16, false>(tasks[lo], static_cast<int>(blockIdx.x) - prefix[lo], 1,
-                                              tasks[lo].blocks_per_problem);
+  project_block<DIMS, 4, 1, MAXT, BF16, false, false, false, C3>(
+      tasks[lo], static_cast<int>(blockIdx.x) - prefix[lo], 1, tasks[lo].blocks_per_problem);
 }
 
 // ---------------------------------------------------------------------------
@@ -2300,7 +2625,7 @@ void launch_k(F kernel, dim3 g, dim3 b, size_t lds, hipStream_t s, KEvents ev, A
                         args...);
 }
 
-template <int DIMS, int AS, int RT, int MAXT, bool BF16>
+template <int DIMS, int AS, int RT, int MAXT, bool BF16, bool C3 = true>
 hipError_t launch_shape(const ProjArgs& a, int total, int threads, size_t lds, hipStream_t s,
                         KEvents ev) {
   if (a.persistent) {
@@ -2309,7 +2634,7 @@ hipError_t launch_shape(const ProjArgs& a, int total, int threads, size_t lds, h
     launch_k(project_kernel<DIMS, AS, RT, MAXT, BF16, true>, dim3(grid), dim3(threads), lds, s, ev,
              a, total);
   } else {
-    launch_k(project_kernel<DIMS, AS, RT, MAXT, BF16, false>, dim3(total), dim3(threads), lds, s,
+    launch_k(project_kernel<DIMS, AS, RT, MAXT, BF16, false, C3>, dim3(total), dim3(threads), lds, s,
              ev, a, total);
   }
   return hipGetLastError();
@@ -2348,6 +2673,7 @@ hipError_t launch_dims(const ProjArgs& a, int total, int threads, size_t lds, hi
     const dim3 g(total), b(threads);
     if (threads <= 512) {
       if (a.resid_hist && a.traj) launch_k(project_special_kernel<DIMS, 512, BF16, true, true>, g, b, lds, s, ev, a, total);
+      else if (a.traj && a.nv <= 12) launch_k(project_special_kernel<DIMS, 512, BF16, false, true, false>, g, b, lds, s, ev, a, total);
       else if (a.traj) launch_k(project_special_kernel<DIMS, 512, BF16, false, true>, g, b, lds, s, ev, a, total);
       else launch_k(project_special_kernel<DIMS, 512, BF16, true, false>, g, b, lds, s, ev, a, total);
     } else {
@@ -2357,21 +2683,37 @@ hipError_t launch_dims(const ProjArgs& a, int total, int threads, size_t lds, hi
     }
     return hipGetLastError();
   }
+  // (at most 12 coefficients per axis: instances without the fourth coefficient
+  // chunk and the branches around it)
+  const bool c3 = a.nv > 12;
+  auto shape = [&](auto as_tag, auto rt_tag, auto maxt_tag) {
+    constexpr int AS = decltype(as_tag)::value, RT = decltype(rt_tag)::value;
+    constexpr int MAXT = decltype(maxt_tag)::value;
+    if constexpr (AS != 8)
+      if (!c3) return launch_shape<DIMS, AS, RT, MAXT, BF16, false>(a, total, threads, lds, s, ev);
+    return launch_shape<DIMS, AS, RT, MAXT, BF16, true>(a, total, threads, lds, s, ev);
+  };
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I4 = std::integral_constant<int, 4>;
+  using I8 = std::integral_constant<int, 8>;
+  using T512 = std::integral_constant<int, 512>;
+  using T1024 = std::integral_constant<int, 1024>;
   if (a.row_tiles == 2) {
     if constexpr (DIMS == 2)
-      if (a.axis_slots == 2) return launch_shape<DIMS, 2, 2, 512, BF16>(a, total, threads, lds, s, ev);
-    return launch_shape<DIMS, 4, 2, 512, BF16>(a, total, threads, lds, s, ev);
+      if (a.axis_slots == 2) return shape(I2{}, I2{}, T512{});
+    return shape(I4{}, I2{}, T512{});
   }
   if (threads <= 512) {
     if constexpr (DIMS == 2)
-      if (a.axis_slots == 2) return launch_shape<DIMS, 2, 1, 512, BF16>(a, total, threads, lds, s, ev);
-    if (a.axis_slots == 8) return launch_shape<DIMS, 8, 1, 512, BF16>(a, total, threads, lds, s, ev);
-    return launch_shape<DIMS, 4, 1, 512, BF16>(a, total, threads, lds, s, ev);
+      if (a.axis_slots == 2) return shape(I2{}, I1{}, T512{});
+    if (a.axis_slots == 8) return shape(I8{}, I1{}, T512{});
+    return shape(I4{}, I1{}, T512{});
   }
   if constexpr (DIMS == 2)
-    if (a.axis_slots == 2) return launch_shape<DIMS, 2, 1, 1024, BF16>(a, total, threads, lds, s, ev);
-  if (a.axis_slots == 8) return launch_shape<DIMS, 8, 1, 1024, BF16>(a, total, threads, lds, s, ev);
-  return launch_shape<DIMS, 4, 1, 1024, BF16>(a, total, threads, lds, s, ev);
+    if (a.axis_slots == 2) return shape(I2{}, I1{}, T1024{});
+  if (a.axis_slots == 8) return shape(I8{}, I1{}, T1024{});
+  return shape(I4{}, I1{}, T1024{});
 }
 
 }  // namespace
@@ -2466,21 +2808,26 @@ hipError_t launch_project_tasks(const ProjTaskLaunch& t, hipStream_t s) {
   const dim3 block(project_threads(t.K, 1));
   const size_t lds = t.lds_bytes;
   const bool bf = t.bf16;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
+  };
   if (block.x <= 512) {
     if (t.dims == 2) {
-      if (bf) hipLaunchKernelGGL((project_task_kernel<2, 512, true>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
-      else hipLaunchKernelGGL((project_task_kernel<2, 512, false>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
+      if (bf) go(project_task_kernel<2, 512, true>);
+      else if (t.nv <= 12) go(project_task_kernel<2, 512, false, false>);
+      else go(project_task_kernel<2, 512, false>);
     } else {
-      if (bf) hipLaunchKernelGGL((project_task_kernel<3, 512, true>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
-      else hipLaunchKernelGGL((project_task_kernel<3, 512, false>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
+      if (bf) go(project_task_kernel<3, 512, true>);
+      else if (t.nv <= 12) go(project_task_kernel<3, 512, false, false>);
+      else go(project_task_kernel<3, 512, false>);
     }
   } else {
     if (t.dims == 2) {
-      if (bf) hipLaunchKernelGGL((project_task_kernel<2, 1024, true>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
-      else hipLaunchKernelGGL((project_task_kernel<2, 1024, false>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
+      if (bf) go(project_task_kernel<2, 1024, true>);
+      else go(project_task_kernel<2, 1024, false>);
     } else {
-      if (bf) hipLaunchKernelGGL((project_task_kernel<3, 1024, true>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
-      else hipLaunchKernelGGL((project_task_kernel<3, 1024, false>), grid, block, lds, s, t.tasks, t.prefix, t.n_tasks);
+      if (bf) go(project_task_kernel<3, 1024, true>);
+      else go(project_task_kernel<3, 1024, false>);
     }
   }
   return hipGetLastError();

@@ -512,7 +512,7 @@ int32_t launch_step(priest_server* s, int slot_index, const std::vector<Req*>& f
   for (const Bucket& b : buckets) {
     const ProjTaskLaunch t{reinterpret_cast<const ProjArgs*>(d + o_proj) + b.first,
                            reinterpret_cast<const int*>(d + o_pre) + b.pre,
-                           b.count, b.blocks, dims, b.K, b.bf, b.lds};
+                           b.count, b.blocks, dims, s->cfg.n_coeff, b.K, b.bf, b.lds};
     SERVE_TRY(launch_project_tasks(t, s->stream));
   }
   {
