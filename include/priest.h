@@ -297,14 +297,14 @@ int32_t priest_plan_batch(priest_problem* p, int32_t n_problems, const float* bc
  * The same projection can be laid out on the GPU in several ways: 4 MFMA
  * columns per sample (4 samples per block) or, in 2D, 2 columns per sample
  * (8 samples per block, two items per lane); one or two 16-step time blocks
- * per wave, or every time block of the horizon in one wave (blocks of 16
- * waves, each with its own samples); one block per tile or a persistent grid
+ * per wave, or every time block of the horizon in one wave (blocks of 8 to
+ * 16 waves, each with its own samples); one block per tile or a persistent grid
  * of resident blocks that loop over tiles (for the whole-horizon shape: one
  * group of samples per wave, or groups that the waves draw from a counter, so
  * that waves whose samples need fewer evaluations take more of them - four
  * per wave from a counter per block, or, in the plan calls, whose workspace
- * then also holds the obstacle records of every problem, from one counter
- * over all (problem, group) pairs of the launch for a grid of resident
+ * then also holds the obstacle records of every problem, from counters
+ * that share all (problem, group) pairs of the launch for a grid of resident
  * blocks).  Every shape gives bit-identical results.  By default the
  * library times every candidate the first time a problem handle meets a new
  * (N, n_problems, sampling mode, precision) - one warm-up and two timed
@@ -324,7 +324,7 @@ typedef struct priest_tiling {
                          batches large enough to fill the chip */
   int32_t persistent; /* 1: grid of resident blocks looping over tiles; with row_tiles 0:
                          sample groups drawn by the waves from a counter (4 per wave and
-                         block; in the plan calls one counter for the whole launch), one
+                         block; in the plan calls counters for the whole launch), one
                          group per wave with 0 */
   int32_t reserved;   /* must be 0 */
 } priest_tiling;

@@ -263,8 +263,8 @@ int32_t check_lds(const priest_problem* p, const ProjArgs& a) {
 
 // Per problem: projected samples, residuals, costs, Cholesky factor, CMA
 // evolution path, status, the obstacle records of a projection launch whose
-// waves draw (problem, group) pairs (3 float4 per obstacle) and that
-// launch's counter (used in problem 0's block only).
+// waves draw (problem, group) pairs (3 float4 per obstacle) and a
+// counter of that launch.
 struct PlanLayout {
   size_t xb, resid, c1, L, pc, status, grec, gq, per_problem;
 };

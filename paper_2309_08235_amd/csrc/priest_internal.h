@@ -38,7 +38,7 @@ struct CostArgs {
 
 struct ProjArgs {
   int32_t dims, nv, K, M, N;
-  int32_t S;                   // samples per block: 16 / axis_slots (x 16 waves for row_tiles 0)
+  int32_t S;                   // samples per block: 16 / axis_slots (x the waves of a block for row_tiles 0)
   int32_t n_iter;              // projection iterations
   int32_t blocks_per_problem;  // ceil(N / S)
   int32_t axis_slots;          // MFMA columns per sample: 4, or 2 (2D only)
@@ -83,9 +83,9 @@ struct ProjArgs {
   float* resid_hist;
   // whole-horizon shape drawing sample groups (persistent = 1): with these
   // set, the launch first writes every problem's obstacle records to `grec`
-  // (3 M float4 per problem, stride in floats) and clears the group counter
-  // `gq`, and the waves of a grid of resident blocks draw (problem, group)
-  // pairs from it; nullable (then each block draws from a counter in LDS)
+  // (3 M float4 per problem, stride in floats) and clears its counter (at
+  // `gq`, with the same stride), and the waves of a grid of resident blocks
+  // draw (problem, group) pairs from them; nullable (then each block draws from a counter in LDS)
   float* grec; int64_t grec_stride;
   int32_t* gq;
 };

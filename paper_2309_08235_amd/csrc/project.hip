@@ -190,7 +190,8 @@ __device__ __forceinline__ void row_max4(float v, float out[4]) {
 
 struct Rec {  // one obstacle record held in (uniform) registers
   float cx, cy, cz, vx, vy, vz, a, a2, ia2, ib2;
-  float mab;  // smaller semi-axis (3D; read only for clearance bounds)
+  float mab;    // smaller semi-axis (3D; read only for clearance bounds)
+  float touch;  // squared (3D: scaled) distance from which no push-out can be positive (rec_at only)
   bool moving;
 };
 
@@ -249,7 +250,7 @@ __device__ __forceinline__ bool pair_push(const Rec& o, float tt, const float p[
 template <int DIMS>
 struct PairTerm {
   float d[DIMS];
-  float f, len2;
+  float q, f, len2;
   float sq;  // sqrt(q) from the same rsq (for clearance bounds; unused otherwise)
 };
 
@@ -261,8 +262,13 @@ struct PairTerm {
 // must stay above the clamp kTiny, which holds for semi-axes up to 1000.
 constexpr float kNudge = 1.0e-15f;
 
-template <int DIMS, bool LAST, bool MOVING>
-__device__ __forceinline__ PairTerm<DIMS> pair_term(const Rec& o, float tt, const float p[DIMS]) {
+// From q = kTouch a^2 (3D: kTouch) on, the factor a rsq(q) - 1 cannot round to
+// a positive one: rsq is within 1 ulp and a^2 is rounded once, so that it would
+// take a q below (1 + 3e-7) a^2.
+constexpr float kTouch = 1.00001f;
+
+template <int DIMS, bool MOVING>
+__device__ __forceinline__ PairTerm<DIMS> pair_offset(const Rec& o, float tt, const float p[DIMS]) {
   PairTerm<DIMS> r;
   if constexpr (MOVING) {
     r.d[0] = p[0] - fmaf(o.vx, tt, o.cx);
@@ -275,23 +281,35 @@ __device__ __forceinline__ PairTerm<DIMS> pair_term(const Rec& o, float tt, cons
   }
   r.d[DIMS == 2 ? 0 : 2] += kNudge;
   const float h = fmaf(r.d[1], r.d[1], r.d[0] * r.d[0]);
-  float q, f;
   if constexpr (DIMS == 2) {
-    q = h;
+    r.q = h;
     r.len2 = h;
-    const float rq = rsq(fmaxf(q, kTiny));
-    f = fmaf(o.a, rq, -1.0f);
-    r.sq = q * rq;
-    if (LAST) f = (q < o.a2) ? f : 0.0f;
   } else {
-    q = fmaf(r.d[2] * r.d[2], o.ib2, h * o.ia2);
+    r.q = fmaf(r.d[2] * r.d[2], o.ib2, h * o.ia2);
     r.len2 = fmaf(r.d[2], r.d[2], h);
-    const float rq = rsq(fmaxf(q, kTiny));
+  }
+  return r;
+}
+
+template <int DIMS, bool LAST>
+__device__ __forceinline__ void pair_factor(const Rec& o, PairTerm<DIMS>& r) {
+  const float rq = rsq(fmaxf(r.q, kTiny));
+  r.sq = r.q * rq;
+  float f;
+  if constexpr (DIMS == 2) {
+    f = fmaf(o.a, rq, -1.0f);
+    if (LAST) f = (r.q < o.a2) ? f : 0.0f;
+  } else {
     f = rq - 1.0f;
-    r.sq = q * rq;
-    if (LAST) f = (q < 1.0f) ? f : 0.0f;
+    if (LAST) f = (r.q < 1.0f) ? f : 0.0f;
   }
   r.f = fmaxf(f, 0.0f);
+}
+
+template <int DIMS, bool LAST, bool MOVING>
+__device__ __forceinline__ PairTerm<DIMS> pair_term(const Rec& o, float tt, const float p[DIMS]) {
+  PairTerm<DIMS> r = pair_offset<DIMS, MOVING>(o, tt, p);
+  pair_factor<DIMS, LAST>(o, r);
   return r;
 }
 
@@ -333,8 +351,7 @@ __device__ __forceinline__ Rec rec_of_lane(const float4& R0, const float4& R1, c
   r.a2 = lane_f(R2.y, b);
   r.ia2 = (DIMS == 3) ? lane_f(R2.z, b) : 0.0f;
   r.ib2 = (DIMS == 3) ? lane_f(R2.w, b) : 0.0f;
-  // (3D keeps b = rsq(1/b^2) in place of a^2)
-  r.mab = (DIMS == 3) ? fminf(lane_f(R2.x, b), r.a2) : r.a;
+  r.mab = (DIMS == 3) ? lane_f(R2.x, b) : r.a;
   return r;
 }
 
@@ -342,9 +359,20 @@ __device__ __forceinline__ Rec rec_of_lane(const float4& R0, const float4& R1, c
 // all of them: a broadcast), with only the fields the push-out of a
 // DIMS-dimensional, static or moving obstacle reads: the same values as
 // rec_of_lane.
-template <int DIMS, bool MOVING>
+// GLOBAL: the table is in global memory and was written by an earlier kernel;
+// with a uniform j it is read through the scalar cache, into SGPRs.
+template <int DIMS, bool MOVING, bool GLOBAL = false>
 __device__ __forceinline__ Rec rec_at(const float4* rec, int M, int j) {
-  const float4 R0 = rec[j], R2 = rec[2 * M + j];
+  auto get = [&](int i) {
+    if constexpr (GLOBAL) {
+      using Uniform = const __attribute__((address_space(4))) f4*;
+      const f4 v = reinterpret_cast<Uniform>(reinterpret_cast<uintptr_t>(rec))[i];
+      return make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+      return rec[i];
+    }
+  };
+  const float4 R0 = get(j), R2 = get(2 * M + j);
   Rec r;
   r.moving = MOVING;
   r.cx = R0.x;
@@ -352,7 +380,7 @@ __device__ __forceinline__ Rec rec_at(const float4* rec, int M, int j) {
   r.cz = (DIMS == 3) ? R0.z : 0.0f;
   r.vx = r.vy = r.vz = 0.0f;
   if constexpr (MOVING) {
-    const float4 R1 = rec[M + j];
+    const float4 R1 = get(M + j);
     r.vx = R1.x;
     r.vy = R1.y;
     r.vz = (DIMS == 3) ? R1.z : 0.0f;
@@ -361,7 +389,8 @@ __device__ __forceinline__ Rec rec_at(const float4* rec, int M, int j) {
   r.a2 = R2.y;
   r.ia2 = (DIMS == 3) ? R2.z : 0.0f;
   r.ib2 = (DIMS == 3) ? R2.w : 0.0f;
-  r.mab = (DIMS == 3) ? fminf(R2.x, R2.y) : R2.x;
+  r.mab = R2.x;
+  r.touch = (DIMS == 3) ? kTouch : R0.z;
   return r;
 }
 
@@ -486,12 +515,14 @@ __device__ void build_records(const float* obs, int M, int t, int nt, float4* re
       v[1] = o[4];
       v[2] = (DIMS == 3) ? o[5] : 0.0f;
       sp = sqrtf(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-      rec[j] = make_float4(c[0], c[1], c[2], fmaxf(a, b) * 1.001f + 1.0e-4f);
+      rec[j] = make_float4(c[0], c[1], DIMS == 3 ? c[2] : a * a * kTouch, fmaxf(a, b) * 1.001f + 1.0e-4f);
       rec[M + j] = make_float4(v[0], v[1], v[2], sp);
     }
-    // 3D keeps rsq(1/b^2), the canonical zero-offset push-out, in place of a^2
-    const float ib2 = 1.0f / (b * b);
-    rec[2 * M + j] = make_float4(a, (DIMS == 3) ? rsq(ib2) : a * a, 1.0f / (a * a), ib2);
+    // 3D keeps the smaller semi-axis in place of a and rsq(1/b^2), the canonical
+    // zero-offset push-out, in place of a^2; 2D keeps the touch threshold in
+    // place of the centre's z
+    const float ib2 = 1.0f / (b * b), rb = rsq(ib2);
+    rec[2 * M + j] = make_float4((DIMS == 3) ? fminf(a, rb) : a, (DIMS == 3) ? rb : a * a, 1.0f / (a * a), ib2);
   }
 }
 
@@ -1680,6 +1711,8 @@ __host__ __device__ inline WaveLayout wave_layout(int dims, int nv, int M, int N
   return l;
 }
 static_assert(2 * 8 * ((3 * kMaxNV + 3) & ~3) <= 12 * kPlane, "a wave's samples fit its planes");
+static_assert(2 * 8 * 2 * kMaxNV + 9 * 2 * kMaxNV <= 12 * kPlane && 2 * 4 * 3 * kMaxNV + 9 * 3 * kMaxNV <= 12 * kPlane,
+              "and nine rows of the factor beside them");
 
 // Wave-wide maximum / minimum of floats that are >= +0 (or +inf / NaN),
 // compared as their bit patterns, which orders them as floats (NaN above
@@ -1820,10 +1853,10 @@ __device__ __forceinline__ uint32_t wave_block_cull(const float4* rec, int M, co
 // nonzero push-out on some valid item; wwv / wwa receive the largest |v|^2 /
 // |a|^2 over the valid items when that row type has none (not in the final
 // pass).
-template <int DIMS, bool LAST, int NI>
+template <int DIMS, bool LAST, int NI, bool GQ>
 __device__ __forceinline__ uint32_t wave_block_push(const float4* rec, int M, float tt, float tmid,
                                                     float thalf, float slack, uint32_t comp,
-                                                    bool test, const bool ok[NI],
+                                                    bool test, bool hot, const bool ok[NI],
                                                     const float p[NI][DIMS], const float v[NI][DIMS],
                                                     const float ac[NI][DIMS], float vmax, float amax,
                                                     const Box& box, float S[NI][DIMS],
@@ -1868,6 +1901,7 @@ __device__ __forceinline__ uint32_t wave_block_push(const float4* rec, int M, fl
         if (!rebuild) pmargin = __uint_as_float(__float_as_uint(mu) & 0x7fffffffu);
       }
       if (rebuild) {
+        hot = false;
         ncand = wave_block_cull<DIMS, NI>(rec, M, p, ok, tmid, thalf, slack, lane, cw);
         pmargin = slack;
       }
@@ -1875,39 +1909,67 @@ __device__ __forceinline__ uint32_t wave_block_push(const float4* rec, int M, fl
     if (ncand) {
       const uint32_t* masks = cw + 32;
       pairs += ncand * nok;
-      float tt_[NI];
+      // HOT (8 samples a wave): some push-out of the block was nonzero at its
+      // last evaluation, so that a budget would not survive this one either: no
+      // clearance is computed, and a candidate that touches no item of the wave
+      // ends after its distances.  (Only inside the grown boxes, where every
+      // valid item is finite.)  64000 2D samples: 3850 -> 3790 us; with 4
+      // samples a wave the branch costs more than it skips (63 scenes of 468
+      // samples: 2545 us with it, 2245 without).
+      int32_t lc[NI];  // (IEEE order of finite floats >= 0 and of any below)
 #pragma unroll
-      for (int i = 0; i < NI; ++i) tt_[i] = tt;
-      for (int g = 0; 64 * g < M; ++g) {
-        const uint4 m4 = *reinterpret_cast<const uint4*>(masks + 4 * g);
-        auto u64 = [](uint32_t lo, uint32_t hi) {
-          return static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lo))) |
-                 (static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(hi))) << 32);
-        };
-        const unsigned long long cmask = u64(m4.x, m4.y);
-        if (!cmask) continue;
-        const unsigned long long mvmask = u64(m4.z, m4.w);
-        unsigned long long ms = cmask & ~mvmask;
-        while (ms) {
-          const Rec o = rec_at<DIMS, false>(rec, M, 64 * g + __builtin_ctzll(ms));
-          ms &= ms - 1;
+      for (int i = 0; i < NI; ++i) lc[i] = 0x7f800000;
+      auto pair = [&](const Rec& o, auto moving_tag, auto hot_tag) {
+        constexpr bool MOVING = decltype(moving_tag)::value, HOT = decltype(hot_tag)::value;
+        PairTerm<DIMS> pt[NI];
+        bool touch = false;
 #pragma unroll
-          for (int i = 0; i < NI; ++i) {
-            const PairTerm<DIMS> pt = pair_term<DIMS, LAST, false>(o, tt_[i], p[i]);
-            pair_add<DIMS, LAST>(o, pt, S[i], r2[i]);
-            if (!LAST) lclear = fminf(lclear, ok[i] ? pair_clearance<DIMS>(o, pt) : INFINITY);
-          }
+        for (int i = 0; i < NI; ++i) {
+          pt[i] = pair_offset<DIMS, MOVING>(o, tt, p[i]);
+          touch = touch | !(pt[i].q >= o.touch);
         }
-        unsigned long long mm = mvmask;
-        while (mm) {
-          const Rec o = rec_at<DIMS, true>(rec, M, 64 * g + __builtin_ctzll(mm));
-          mm &= mm - 1;
+        if constexpr (HOT)
+          if (wballot(touch) == 0ull) return;
 #pragma unroll
-          for (int i = 0; i < NI; ++i) {
-            const PairTerm<DIMS> pt = pair_term<DIMS, LAST, true>(o, tt_[i], p[i]);
-            pair_add<DIMS, LAST>(o, pt, S[i], r2[i]);
-            if (!LAST) lclear = fminf(lclear, ok[i] ? pair_clearance<DIMS>(o, pt) : INFINITY);
-          }
+        for (int i = 0; i < NI; ++i) {
+          pair_factor<DIMS, LAST>(o, pt[i]);
+          pair_add<DIMS, LAST>(o, pt[i], S[i], r2[i]);
+          if constexpr (!LAST && !HOT) lc[i] = min(lc[i], __float_as_int(pair_clearance<DIMS>(o, pt[i])));
+        }
+      };
+      auto list = [&](unsigned long long m, int g, auto moving_tag, auto hot_tag) {
+        constexpr bool MOVING = decltype(moving_tag)::value;
+        auto get = [&] { return rec_at<DIMS, MOVING, GQ>(rec, M, 64 * g + __builtin_ctzll(m)); };
+        while (m) {
+          const Rec o = get();
+          m &= m - 1;
+          pair(o, moving_tag, hot_tag);
+        }
+      };
+      auto lists = [&](auto hot_tag) {
+        for (int g = 0; 64 * g < M; ++g) {
+          const uint4 m4 = *reinterpret_cast<const uint4*>(masks + 4 * g);
+          auto u64 = [](uint32_t lo, uint32_t hi) {
+            return static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lo))) |
+                   (static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(hi))) << 32);
+          };
+          const unsigned long long cmask = u64(m4.x, m4.y);
+          if (!cmask) continue;
+          const unsigned long long mvmask = u64(m4.z, m4.w);
+          list(cmask & ~mvmask, g, std::false_type{}, hot_tag);
+          list(mvmask, g, std::true_type{}, hot_tag);
+        }
+      };
+      if (NI == 2 && !LAST && hot) {
+        lists(std::true_type{});
+        lclear = -1.0f;
+      } else {
+        lists(std::false_type{});
+        if constexpr (!LAST) {
+          int32_t m = 0x7f800000;
+#pragma unroll
+          for (int i = 0; i < NI; ++i) m = ok[i] ? min(m, lc[i]) : m;
+          lclear = __int_as_float(m);
         }
       }
     }
@@ -2030,14 +2092,21 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
   // The tile's groups of SPW samples are drawn by the block's waves from a
   // counter in LDS: a wave that finishes a group early takes the next one
   // instead of idling until the slowest wave of the block is done.  With GQ
-  // the waves of every block draw (problem, group) pairs from one counter in
-  // global memory for the whole launch (total = the number of pairs), with
-  // the problems' obstacle records in global memory too, so no block waits
-  // for its waves before the end of the launch.
+  // the waves of every block draw (problem, group) pairs of the whole launch
+  // (total = their number), with the problems' obstacle records in global
+  // memory too, so no block waits for its waves before the end of the launch.
+  // The pairs are dealt round to the problems' counters (at most 64), which the
+  // waves share evenly; one whose counter has run out moves to another.  (A
+  // single counter takes an add every 20 ns: 4096 waves that start together, or
+  // groups of short work, wait for it.)
   int* ctr = reinterpret_cast<int*>(sm + l.ctr);
   float* sMu = sm + l.mul;
   float* sL = sMu + D4;
   const int gpp = (a.N + SPW - 1) / SPW;  // groups per problem
+  const int counters = GQ ? min(total / gpp, 64) : 1;
+  auto counter = [&](int c) { return a.gq + c * a.grec_stride; };
+  [[maybe_unused]] int home = 0;  // the counter this wave draws from
+  if constexpr (GQ) home = (first * WPB + __builtin_amdgcn_readfirstlane(w)) % counters;
   // (the W table is complete before any wave reads it; without GQ the first
   // barrier of the tile loop does this)
   if constexpr (GQ) __syncthreads();
@@ -2067,10 +2136,23 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
     }
     for (;;) {
       int gi = 0;
-      if (lane == 0) gi = atomicAdd(GQ ? a.gq : ctr, 1);
+      if (lane == 0) gi = atomicAdd(GQ ? counter(home) : ctr, 1);
       gi = __builtin_amdgcn_readfirstlane(gi);
       if constexpr (GQ) {
-        if (gi >= total) break;
+        gi = gi * counters + home;
+        if (gi >= total) {
+          // the next counter with a pair left, if any.  (One seen at its end
+          // stays there, so this ends after one failed add a counter at most.)
+          int c = home + 1 + lane;
+          if (c >= counters) c -= counters;
+          bool left = lane < counters - 1;
+          if (left)
+            left = __hip_atomic_load(counter(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * counters + c < total;
+          const unsigned long long m = wballot(left);
+          if (!m) break;
+          home = __builtin_amdgcn_readlane(c, __builtin_ctzll(m));
+          continue;
+        }
         prob = gi / gpp;
         gi -= prob * gpp;
       } else {
@@ -2104,16 +2186,50 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
             *reinterpret_cast<float4*>(sZ + s * D4 + 4 * qq) = make_float4(z[0], z[1], z[2], z[3]);
           }
         }
-        wave_lds_sync();
-        for (int i = lane; i < nsw * D; i += 64) {
-          const int s = i / D, d = i - s * D;
-          const float* zz = sZ + s * D4;
-          const float* Lr = LP + d * D;
-          float x = muP[d];
-          for (int e = 0; e <= d; ++e) x = fmaf(Lr[e], zz[e], x);
-          xs[s * D4 + d] = x;
+        // xi = mu + L z, a fused multiply-add per column in ascending order.
+        // With GQ the factor's rows are staged in what the samples leave of the
+        // planes, as many as fit (at least 9), so that global memory is read
+        // once and in order.
+        float* sLw = sZ + SPW * D4;
+        const int R = GQ ? min(D, (12 * kPlane - 2 * SPW * D4) / D) : D;
+        for (int r0 = 0; r0 < D; r0 += R) {
+          const int nr = min(R, D - r0);
+          if constexpr (GQ) {
+            const float* src = LP + r0 * D;
+            const int n = nr * D;
+            for (int i0 = 0; i0 < n; i0 += 64 * 8) {
+              float v[8];
+#pragma unroll
+              for (int j = 0; j < 8; ++j) v[j] = src[min(i0 + 64 * j + lane, n - 1)];
+#pragma unroll
+              for (int j = 0; j < 8; ++j)
+                if (i0 + 64 * j + lane < n) sLw[i0 + 64 * j + lane] = v[j];
+            }
+          }
+          wave_lds_sync();
+          for (int i = lane; i < nsw * nr; i += 64) {
+            const int s = i / nr, dr = i - s * nr, d = r0 + dr;
+            const float* zz = sZ + s * D4;
+            const float* Lr = GQ ? sLw + dr * D : LP + d * D;
+            float x = muP[d];
+            // (four columns a step; those past d, up to three of them past the
+            // row, are read and not used)
+            for (int e = 0; e < r0 + nr; e += 4) {
+              const float4 z4 = *reinterpret_cast<const float4*>(zz + e);
+              const float zv[4] = {z4.x, z4.y, z4.z, z4.w};
+              float lv[4];
+#pragma unroll
+              for (int c = 0; c < 4; ++c) lv[c] = Lr[e + c];
+#pragma unroll
+              for (int c = 0; c < 4; ++c) {
+                const float y = fmaf(lv[c], zv[c], x);
+                x = e + c <= d ? y : x;
+              }
+            }
+            xs[s * D4 + d] = x;
+          }
+          wave_lds_sync();
         }
-        wave_lds_sync();
         if (a.xi_src) {
           float* dst = a.xi_src + prob * a.xi_src_stride + static_cast<int64_t>(gs0) * D;
           for (int i = lane; i < nsw * D; i += 64) dst[i] = xs[(i / D) * D4 + i % D];
@@ -2165,6 +2281,7 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
       uint32_t ncl = ~0u;  // no cache yet
       const uint32_t blocks = (1u << NB) - 1u;
       uint32_t mP = blocks, mV = blocks, mA = blocks;  // blocks to evaluate
+      uint32_t hotm = 0;  // blocks with an obstacle's push-out at their last test
       float X;
       {
         float m = 0.0f;
@@ -2181,7 +2298,7 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
       // One time block: forward rows of the row types in `comp` (bit 0:
       // positions, 1: velocities, 2: accelerations) of columns 4 q + 0..3 at
       // step 16 tb + ti (item layout), then the push-outs of this lane's items.
-      auto block_items = [&](int tb, uint32_t comp, bool test, uint32_t& ncand, auto last_tag,
+      auto block_items = [&](int tb, uint32_t comp, bool test, bool hot, uint32_t& ncand, auto last_tag,
                              float p[NI][DIMS], float v[NI][DIMS], float ac[NI][DIMS],
                              float S[NI][DIMS], float dv[NI][DIMS], float da[NI][DIMS], float r2[NI],
                              bool ok[NI], float& wwv, float& wwa, float& pm, float& lcl) {
@@ -2231,8 +2348,8 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
           }
         }
         const float tmid = a.dt * (static_cast<float>(16 * tb) + 7.5f);
-        return wave_block_push<DIMS, LAST, NI>(recp, M, a.dt * static_cast<float>(t), tmid, thalf, slack,
-                                               comp, test, ok, p, v, ac, a.vmax, a.amax, a.box, S,
+        return wave_block_push<DIMS, LAST, NI, GQ>(recp, M, a.dt * static_cast<float>(t), tmid, thalf, slack,
+                                               comp, test, hot, ok, p, v, ac, a.vmax, a.amax, a.box, S,
                                                dv, da, r2, lane, cwords + tb * cstride, ncand, nok,
                                                pairs, wwv, wwa, pm, lcl);
       };
@@ -2261,13 +2378,14 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
             float p[NI][DIMS], v[NI][DIMS], ac[NI][DIMS], S[NI][DIMS], dv[NI][DIMS], da[NI][DIMS], r2[NI];
             bool ok[NI];
             float wwv = 0.0f, wwa = 0.0f, pm = 0.0f, lcl = INFINITY;
-            const uint32_t nz = block_items(tb, comp, test, ncand, std::false_type{}, p, v, ac, S, dv,
+            const uint32_t nz = block_items(tb, comp, test, test && (hotm & bit) != 0u, ncand, std::false_type{}, p, v, ac, S, dv,
                                             da, r2, ok, wwv, wwa, pm, lcl);
             // new budgets of the row types evaluated here; the position budget
             // is the smaller of the grown-box margin (per axis) and the
             // candidates' clearance (Euclidean, over sqrt(dims)), or none while
             // some position push-out is nonzero
             if (test) {
+              hotm = (nz & 1u) ? hotm | bit : hotm & ~bit;
               float bp = -1.0f;
               if (!(nz & 1u)) {
                 // (one reduction of both: rounding is monotone, so the smallest
@@ -2417,7 +2535,7 @@ __device__ __forceinline__ void project_wave_block(const ProjArgs& a, int first,
         bool ok[NI];
         uint32_t ncand = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(ncl), tb));
         float wwv = 0.0f, wwa = 0.0f, pm = 0.0f, lcl = INFINITY;
-        block_items(tb, 7u, (mP >> tb) & 1u, ncand, std::true_type{}, p, v, ac, S, dv, da, r2, ok, wwv,
+        block_items(tb, 7u, (mP >> tb) & 1u, false, ncand, std::true_type{}, p, v, ac, S, dv, da, r2, ok, wwv,
                     wwa, pm, lcl);
         // per-(t, sample) residual^2 and cost through this wave's planes
 #pragma unroll
@@ -2485,14 +2603,13 @@ __global__ __launch_bounds__(1024) void project_wave_kernel(ProjArgs a, int tota
 }
 
 // Before a launch that draws (problem, group) pairs from global memory: each
-// problem's obstacle records (one block per problem), and the counter set to
-// zero.
+// problem's obstacle records (one block per problem), and its counter's zero.
 template <int DIMS>
 __global__ void wave_records_kernel(ProjArgs a) {
   const int prob = blockIdx.x;
   build_records<DIMS>(a.obs + prob * a.obs_stride, a.M, threadIdx.x, blockDim.x,
                       reinterpret_cast<float4*>(a.grec + prob * a.grec_stride));
-  if (prob == 0 && threadIdx.x == 0) *a.gq = 0;
+  if (threadIdx.x == 0) a.gq[prob * a.grec_stride] = 0;
 }
 
 // Per-row push-outs e(xi) - F xi, [N][M + 2][K][dims] (parity hook): one
@@ -2644,8 +2761,8 @@ template <int DIMS, int AS, bool BF16>
 hipError_t launch_wave_shape(const ProjArgs& a, int total, int threads, size_t lds, hipStream_t s,
                              KEvents ev) {
   if (a.persistent && a.gq && a.grec && !a.traj) {
-    // one counter over every (problem, group) pair of the launch, drawn by
-    // the waves of a grid of resident blocks
+    // every (problem, group) pair of the launch, drawn by the waves of a grid
+    // of resident blocks
     const int P = total / a.blocks_per_problem;
     const int pairs = P * ((a.N + 16 / AS - 1) / (16 / AS));
     hipLaunchKernelGGL(wave_records_kernel<DIMS>, dim3(P), dim3(256), 0, s, a);
@@ -2747,10 +2864,14 @@ size_t wave_lds_bytes(const ProjArgs& a, int wpb) {
          static_cast<size_t>(wave_layout(a.dims, a.nv, a.M, (a.K + 15) / 16, wpb, a.mode).total);
 }
 
-// Waves per block of the whole-horizon shape: the most (16, 12, 8 or 4)
-// whose LDS (the block's W table and records, a region per wave) fits.
+// Waves per block of the whole-horizon shape: 8 if the LDS of two such blocks
+// (a W table and records each, a region per wave) fits a CU, which then holds
+// 16 waves as with one block of 16 but has only 8 wait for a block's slowest
+// (64000 2D samples: 3790 us with blocks of 16, 3690 with 8; with blocks of 4,
+// three a CU, 4400).  Otherwise the most of 16, 12, 8 and 4 that fit.
 int wave_block_waves(const ProjArgs& a) {
   const size_t limit = device_lds_limit();
+  if (2 * wave_lds_bytes(a, 8) <= limit) return 8;
   for (int wpb : {16, 12, 8})
     if (wave_lds_bytes(a, wpb) <= limit) return wpb;
   return 4;
