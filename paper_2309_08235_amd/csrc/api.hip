@@ -442,6 +442,87 @@ int32_t enqueue_plan(int32_t P, PlanArgs pa, const priest_cem_params* c, const f
   return PRIEST_OK;
 }
 
+// The plan loop's arguments for the problems from p0 on.
+void skip_problems(int32_t p0, PlanArgs& pa, const float*& noise, priest_plan_out& out) {
+  auto skip = [&](auto& ptr, int64_t stride) {
+    if (ptr) ptr += p0 * stride;
+  };
+  ProjArgs& a = pa.a;
+  CemArgs& ca = pa.ca;
+  const int64_t ND = static_cast<int64_t>(ca.N) * ca.D;
+  a.stream_base += static_cast<uint32_t>(p0);
+  skip(a.bc, a.bc_stride);
+  skip(a.obs, a.obs_stride);
+  skip(a.mu, a.mu_stride);
+  skip(a.L, a.L_stride);
+  skip(a.noise, a.noise_stride);
+  skip(a.xi_out, a.xi_out_stride);
+  skip(a.resid, a.n_stride);
+  skip(a.c1, a.n_stride);
+  skip(a.grec, a.grec_stride);
+  skip(a.gq, a.grec_stride);
+  skip(ca.xb, ca.xb_stride);
+  skip(ca.resid, ca.n_stride);
+  skip(ca.c1, ca.n_stride);
+  skip(ca.mu, ca.mu_stride);
+  skip(ca.cov, ca.cov_stride);
+  skip(ca.L, ca.L_stride);
+  skip(ca.pc, ca.pc_stride);
+  skip(ca.best_xi, ca.best_stride);
+  skip(ca.best_cost, 1);
+  skip(ca.elite_idx, ca.n_elite);
+  skip(ca.proj_idx, ca.n_proj);
+  skip(ca.status, 1);
+  skip(noise, a.noise_stride);
+  skip(out.xi, ND);
+  skip(out.xi_bar, ND);
+  skip(out.resid, ca.N);
+  skip(out.c1, ca.N);
+}
+
+// Whether a captured plan loop runs its problems in two halves, side by side:
+// one half's refits, and the end of its projections, where blocks wait for the
+// slowest samples, then overlap the other's projections.  Measured, one chain
+// against two, by the launch's waves over those that the device holds (16 a
+// CU): 0.85 (4 2D problems of 1000 samples) 5.03 -> 5.26 ms, 0.98 (8 3D of
+// 2000) 12.6 -> 12.6, 1.2 (64 3D of 300) 16.9 -> 13.9, 1.7 (8 2D of 1000) 9.8
+// -> 8.4, 2.0 (64 2D of 1000) 69 -> 56, 3.9 (64 3D of 1000) 29.3 -> 29.5, 5.9
+// (96 2D of 2000) 169 -> 168, 7.8 (64 3D of 2000) 52.2 -> 54.5.  Four parts
+// took as long as two.
+bool halves_pay(const ProjArgs& a, int32_t P) {
+  if (P < 2) return false;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return false;
+  const int spw = 16 / a.axis_slots;
+  const int64_t waves = a.row_tiles == 0
+                            ? static_cast<int64_t>(P) * ((a.N + spw - 1) / spw)
+                            : static_cast<int64_t>(P) * a.blocks_per_problem * (project_threads(a.K, a.row_tiles) / 64);
+  const int64_t held = 16 * static_cast<int64_t>(cus);
+  return waves > held && waves < 3 * held;
+}
+
+// The plan loop captured as two chains of half the problems each, the second
+// one on a stream of its own that forks from s and joins it again.
+int32_t capture_halves(int32_t P, const PlanArgs& pa, const priest_cem_params* c, const float* noise,
+                       const priest_plan_out* out, hipStream_t s, hipStream_t side, hipEvent_t fork,
+                       hipEvent_t join) {
+  const int32_t p0 = P / 2;
+  HIP_TRY(hipEventRecord(fork, s));
+  HIP_TRY(hipStreamWaitEvent(side, fork, 0));
+  PlanArgs second = pa;
+  const float* noise2 = noise;
+  priest_plan_out out2 = *out;
+  skip_problems(p0, second, noise2, out2);
+  int32_t st = enqueue_plan(p0, pa, c, noise, out, s);
+  if (st == PRIEST_OK) st = enqueue_plan(P - p0, second, c, noise2, &out2, side);
+  // (also after a failure: the capture ends with every stream joined)
+  HIP_TRY(hipEventRecord(join, side));
+  HIP_TRY(hipStreamWaitEvent(s, join, 0));
+  return st;
+}
+
 bool tiling_cached(priest_problem* p, const ProjArgs& a, int P) {
   std::lock_guard<std::mutex> lk(p->tune_mu);
   if (p->forced) return true;
@@ -908,10 +989,29 @@ static int32_t plan_common(priest_problem* p, int32_t P, const float* bc, const 
       HIP_TRY(hipGraphLaunch(g.exec, s));
       return PRIEST_OK;
     }
-  HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-  st = enqueue_plan(P, pa, c, noise, out, s);
+  // (the side stream and events exist for the capture only; without them the
+  // loop is captured as one chain)
+  hipStream_t side = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
+  const bool halves = halves_pay(pa.a, P) && !stream_capturing(s) &&
+                      hipStreamCreateWithFlags(&side, hipStreamNonBlocking) == hipSuccess &&
+                      hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
+                      hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess;
+  auto release = [&] {
+    if (join) (void)hipEventDestroy(join);
+    if (fork) (void)hipEventDestroy(fork);
+    if (side) (void)hipStreamDestroy(side);
+  };
+  const hipError_t be = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+  if (be != hipSuccess) {
+    release();
+    HIP_TRY(be);
+  }
+  st = halves ? capture_halves(P, pa, c, noise, out, s, side, fork, join)
+              : enqueue_plan(P, pa, c, noise, out, s);
   hipGraph_t graph = nullptr;
   const hipError_t ce = hipStreamEndCapture(s, &graph);
+  release();
   if (st != PRIEST_OK) {
     if (graph) (void)hipGraphDestroy(graph);
     return st;
