@@ -540,11 +540,17 @@ __device__ __forceinline__ int coef_of(int q, int r) { return r < 3 ? 3 * q + r 
 // remaining slots empty.  (16, 8), (8, 4), (32, 8), (32, 16) and (12, 6): a
 // 1000-sample 2D projection of 100 iterations took 179, 194, 183, 181 and
 // 186 us, a 20 x 100 plan 2.96, 2.95, 2.97, 3.04 and 2.94 ms.
+//
+// A search takes some hundred cycles per obstacle in reach, which a launch of
+// few iterations among many obstacles does not earn back: with more than three
+// obstacles per iteration it looks kNearReach units far (138 obstacles, 34
+// iterations: a 4 x 34 plan 966 us with 16 units, 868 with 8; 106 and 15: 2140,
+// 1990; but 69 and 29: 207, 220, and 37 and 35: 413, 435).
 #ifndef PRIEST_CULL_SLACK
 #define PRIEST_CULL_SLACK 0.25f
 #endif
 constexpr float kSlack = PRIEST_CULL_SLACK;
-constexpr float kReach = 16.0f, kRoomy = 8.0f;
+constexpr float kReach = 16.0f, kRoomy = 8.0f, kNearReach = 8.0f;
 
 // Obstacles an item keeps between iterations: its nearest ones, in registers.
 constexpr int lane_slots(int dims) { return dims == 2 ? 4 : 3; }
@@ -577,6 +583,7 @@ struct Scene {
   int M, K;
   float unit;    // kSlack * (smallest cull radius of the scene)
   float thalf;   // half the time window of a row of 16 lanes
+  float reach;   // of a search
 };
 
 // Centre of obstacle j at item i's time (a static obstacle's comes unchanged).
@@ -591,6 +598,11 @@ __device__ __forceinline__ void centre_at(const Scene& sc, const TimeBlock<NI, D
 #pragma unroll
     for (int x = 0; x < DIMS; ++x) oc[x] = fmaf(v[x], tb.tt[i], c[x]);
   }
+}
+
+// Median of three (v_med3_u32).
+__device__ __forceinline__ uint32_t med3(uint32_t a, uint32_t b, uint32_t c) {
+  return max(min(a, b), min(max(a, b), c));
 }
 
 // Calls fn(record, cull radius, index, moving) for the obstacles named by the
@@ -661,7 +673,7 @@ __device__ __forceinline__ void search_obstacles(const Scene& sc, TimeBlock<NI, 
                                                  bool count) {
   constexpr int L = TimeBlock<NI, DIMS>::L;
   const int M = sc.M;
-  const float reach = sc.unit * kReach;
+  const float reach = sc.reach;
   float lo[DIMS][4], hi[DIMS][4];
 #pragma unroll
   for (int x = 0; x < DIMS; ++x) {
@@ -727,13 +739,12 @@ __device__ __forceinline__ void search_obstacles(const Scene& sc, TimeBlock<NI, 
       }
       // (a distance that is not a finite number counts as none at all)
       const float gap = d2 < INFINITY ? fmaxf(fmaf(__builtin_amdgcn_sqrtf(d2), 0.999999f, -cull), 0.0f) : 0.0f;
-      uint32_t t = (__float_as_uint(gap) & ~2047u) | rank;
+      const uint32_t t = (__float_as_uint(gap) & ~2047u) | rank;
+      // (insertion into an ascending list: each place takes the median of what
+      // it holds, what its predecessor holds and the new key)
 #pragma unroll
-      for (int k = 0; k <= L; ++k) {
-        const uint32_t a = key[i][k] < t ? key[i][k] : t;
-        t = key[i][k] < t ? t : key[i][k];
-        key[i][k] = a;
-      }
+      for (int k = L; k > 0; --k) key[i][k] = med3(key[i][k - 1], t, key[i][k]);
+      key[i][0] = min(key[i][0], t);
     }
   });
   auto gap_of = [&](uint32_t k) { return k == ~0u ? INFINITY : __uint_as_float(k & ~2047u); };
@@ -1172,11 +1183,12 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
     }
     xb = xi;
     f4 lam = {0.0f, 0.0f, 0.0f, 0.0f};
-    Scene sc{rec, a.obs + prob * a.obs_stride, M, K, 0.0f, a.dt * 1.5f};
+    Scene sc{rec, a.obs + prob * a.obs_stride, M, K, 0.0f, a.dt * 1.5f, 0.0f};
     {
       float cmin = INFINITY;
       for (int j = lane; j < M; j += 64) cmin = fminf(cmin, rec[j].w);
       sc.unit = kSlack * wave_min(cmin);
+      sc.reach = sc.unit * (M > 3 * a.n_iter ? kNearReach : kReach);
     }
     uint32_t pairs = 0;
     // Budgets (per lane, in units of max|Delta xi_bar| of the lane's sample):
