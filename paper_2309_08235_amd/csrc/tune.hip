@@ -12,7 +12,7 @@
 // candidate runs one warm-up launch of one iteration, then two timed launches of
 // the caller's real arguments (outputs redirected by the caller), with HIP
 // events on the caller's stream; those within kAgain of the fastest run a second
-// pass and keep their faster one, and the fastest candidate is kept (by a 5%
+// pass and keep their faster one, and the fastest candidate is kept (by a 3%
 // margin).
 #include <algorithm>
 #include <vector>
@@ -81,11 +81,11 @@ hipError_t time_tilings(const ProjArgs& trial, int n_problems, size_t lds_limit,
 }
 
 int pick_tiling(const std::vector<float>& ms) {
-  // a candidate replaces the current pick only if it is more than 5% faster,
+  // a candidate replaces the current pick only if it is more than 3% faster,
   // so timing noise between near-equal shapes does not flip the choice
   int best = 0;
   for (size_t i = 1; i < ms.size(); ++i)
-    if (ms[i] >= 0.0f && (ms[best] < 0.0f || ms[i] < ms[best] * 0.95f)) best = static_cast<int>(i);
+    if (ms[i] >= 0.0f && (ms[best] < 0.0f || ms[i] < ms[best] * 0.97f)) best = static_cast<int>(i);
   return best;
 }
 
