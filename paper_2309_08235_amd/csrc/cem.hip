@@ -27,6 +27,7 @@
 // Every sum runs in a fixed order, so results are bitwise reproducible.
 #include "priest_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace priest {
@@ -46,10 +47,8 @@ struct CemLayout {
   size_t proj, elite, w, red, mu, pc, A, mu0, cov0, pc0, stage, cen, total;
 };
 
-// small: at most 2048 samples; up_to: the largest stage of any number of elites
-// up to n_elite (launches of several problems of their own sizes).
-__host__ __device__ inline CemLayout cem_layout(int D, int n_proj, int n_elite, bool small,
-                                                bool up_to = false) {
+// small: at most 2048 samples.
+__host__ __device__ inline CemLayout cem_layout(int D, int n_proj, int n_elite, bool small) {
   CemLayout l{};
   size_t o = 0;
   l.proj = o;  o += align16(sizeof(int) * (n_proj > 0 ? n_proj : 1));
@@ -64,7 +63,7 @@ __host__ __device__ inline CemLayout cem_layout(int D, int n_proj, int n_elite, 
   l.pc0 = o;   o += align16(sizeof(float) * D);
   const size_t rows = static_cast<size_t>(n_elite) * D;
   size_t staged = kStageFloats;
-  if (small && rows > kStageFloats && (rows <= kRawFloats || up_to)) staged = rows < kRawFloats ? rows : kRawFloats;
+  if (small && rows > kStageFloats && rows <= kRawFloats) staged = rows;
   l.stage = o; o += align16(sizeof(float) * staged);
   l.cen = o;   o += small ? sizeof(float) * 2 * kCenRows * kCenCols : 0;
   l.total = o;
@@ -1003,7 +1002,11 @@ static void launch_task_dm(const CemTaskLaunch& t, size_t lds, hipStream_t s) {
 }
 
 hipError_t launch_cem_tasks(const CemTaskLaunch& t, hipStream_t s) {
-  const size_t lds = cem_layout(t.D, t.max_N, t.max_elite, t.max_N <= kCemThreads * 4, true).total;
+  // the most that any number of elites up to the largest takes: that of the
+  // largest, or of the most whose rows are all staged
+  const bool small = t.max_N <= kCemThreads * 4;
+  const size_t lds = std::max(cem_layout(t.D, t.max_N, t.max_elite, small).total,
+                              cem_layout(t.D, t.max_N, std::min(t.max_elite, kRawFloats / t.D), small).total);
   if (t.D <= 24) launch_task_dm<24>(t, lds, s);
   else if (t.D <= 36) launch_task_dm<36>(t, lds, s);
   else launch_task_dm<48>(t, lds, s);

@@ -65,3 +65,36 @@ def test_refit_of_all_staged_elites_or_one_more(n_coeff, n_elite):
     _check_cem_step(oracle_problem(wl), bc, obs, wl, cem, mu0, cov0, noise[0], out, np64(mu), np64(cov),
                     f"n_coeff={n_coeff} n_elite={n_elite}")
     gp.close()
+
+
+def test_served_refits_of_mixed_sizes():
+    """Requests of one server step share a refit launch: the largest number of
+    elites of the largest problems (D = 48) beside few, and beside as many as
+    have all rows staged, with the results of each request alone."""
+    from paper_2309_08235_amd import serve as S
+    sw = W.ServingWorkload(dims=3, n_coeff=16, n_proj_iters=4, n_cem=2, n_robots=3)
+    bc = np.zeros((3, 6))
+    bc[:, 3] = 7.0
+    obs = np.zeros((3, 8))
+    obs[:, :3] = np.array([[2, 2, 3], [4, 5, 4], [5, 4, 6]])
+    obs[:, 6] = obs[:, 7] = 0.5
+    reqs = [W.ServingRequest(index=i, robot=i, arrival=0.0, n_samples=n, n_obs=3, n_steps=50, horizon=10.0,
+                             n_proj=n_proj, n_elite=n_elite, bc=bc, obs=obs)
+            for i, (n, n_proj, n_elite) in enumerate([(2048, 2048, 2048), (1000, 700, 256), (64, 40, 5)])]
+
+    def serve(rs):
+        s = S.Server.for_workload(sw, max_active=8, max_robots=3, memory_budget=64 << 20, seed=9)
+        for q in rs:
+            s.submit_request(q, sw, warm_start=1)
+        done = s.drain()
+        s.close()
+        return {c.request_id: c for c in done}
+
+    print("served refits: 2048, 256 and 5 elites, D = 48", flush=True)
+    mixed = serve(reqs)
+    assert len(mixed) == 3
+    for k, q in enumerate(reqs):
+        alone = serve([q])[1]
+        assert alone.status == 0 and mixed[k + 1].status == 0
+        assert alone.best_cost == mixed[k + 1].best_cost
+        np.testing.assert_array_equal(alone.best_xi, mixed[k + 1].best_xi)
