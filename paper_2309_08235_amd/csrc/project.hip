@@ -543,9 +543,10 @@ __device__ __forceinline__ int coef_of(int q, int r) { return r < 3 ? 3 * q + r 
 //
 // A search takes some hundred cycles per obstacle in reach, which a launch of
 // few iterations among many obstacles does not earn back: with more than three
-// obstacles per iteration it looks kNearReach units far (138 obstacles, 34
-// iterations: a 4 x 34 plan 966 us with 16 units, 868 with 8; 106 and 15: 2140,
-// 1990; but 69 and 29: 207, 220, and 37 and 35: 413, 435).
+// obstacles per two iterations it looks kNearReach units far (124 obstacles, 76
+// iterations: a 10 x 76 plan of 18 problems 4820 us with 16 units, 4300 with 8;
+// 138 and 34: 966, 868; 113 and 60: 294, 255; but 69 and 29: 207, 223, and 37
+// and 35: 413, 435).
 #ifndef PRIEST_CULL_SLACK
 #define PRIEST_CULL_SLACK 0.25f
 #endif
@@ -1188,7 +1189,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       float cmin = INFINITY;
       for (int j = lane; j < M; j += 64) cmin = fminf(cmin, rec[j].w);
       sc.unit = kSlack * wave_min(cmin);
-      sc.reach = sc.unit * (M > 3 * a.n_iter ? kNearReach : kReach);
+      sc.reach = sc.unit * (2 * M > 3 * a.n_iter ? kNearReach : kReach);
     }
     uint32_t pairs = 0;
     // Budgets (per lane, in units of max|Delta xi_bar| of the lane's sample):
