@@ -26,6 +26,7 @@
 //      draw: one wave, a rank-1 MFMA per column.
 // Every sum runs in a fixed order, so results are bitwise reproducible.
 #include "priest_internal.h"
+#include "quotient.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -743,9 +744,8 @@ __device__ __forceinline__ void cem_block(const CemArgs& a, int prob) {
     const int wv = tid >> 6, lane = tid & 63;
     // every row is staged (raw) or one chunk of them at a time
     const bool raw = one_chunk || (kPre && a.n_elite * D <= kRawFloats);
-    // (16 loads per thread in flight; i / D by the high half of i ceil(2^32 / D),
-    // exact below 2^16)
-    const uint32_t inv_d = 0xffffffffu / static_cast<uint32_t>(D) + 1u;
+    // (16 loads per thread in flight)
+    const uint32_t inv_d = inverse_of(static_cast<uint32_t>(D));
     auto stage_rows = [&](int m0, int nm) {
       constexpr int kG = 16;
       const int n = nm * D;
@@ -755,7 +755,7 @@ __device__ __forceinline__ void cem_block(const CemArgs& a, int prob) {
         for (int u = 0; u < kG; ++u)
           if (b + u * kCemThreads < n) {
             const int i = min(b + u * kCemThreads + tid, n - 1);
-            const int m = static_cast<int>(__umulhi(static_cast<uint32_t>(i), inv_d));
+            const int m = static_cast<int>(quotient(static_cast<uint32_t>(i), inv_d));
             v[u] = xb[elite[m0 + m] * D + (i - m * D)];
           }
 #pragma unroll
