@@ -40,6 +40,7 @@ struct ProjArgs {
   int32_t dims, nv, K, M, N;
   int32_t S;                   // samples per block: 16 / axis_slots (x the waves of a block for row_tiles 0)
   int32_t n_iter;              // projection iterations
+  int32_t trial_of;            // > 0: a tile-shape trial, cut short, of a launch of so many iterations
   int32_t blocks_per_problem;  // ceil(N / S)
   int32_t axis_slots;          // MFMA columns per sample: 4, or 2 (2D only)
   int32_t row_tiles;           // 16-step time blocks per wave: 1 or 2; 0: the whole horizon

@@ -103,13 +103,13 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 struct Layout {  // offsets into dynamic LDS, in floats
-  int rec, gp, fin, hist, cm, first, mu, L, z, xs, total;
+  int rec, gp, fin, hist, cm, first, flag, mu, L, z, xs, total;
 };
 
 // rec: obstacle records (three float4 arrays of M, structure of arrays); gp:
 // double-buffered partial right-hand sides (256 per 16-step block); fin: per-(t, sample) residual^2 and c1 of the final pass;
-// cm: per-wave obstacle candidate masks (4 words per 64 obstacles); xs: the
-// block's samples; mu/L/z: sampler staging.  NB = 16-step blocks of the
+// cm: per-wave obstacle candidate masks (4 words per 64 obstacles); flag: three
+// words per wave for the choice of the loop; xs: the block's samples; mu/L/z: sampler staging.  NB = 16-step blocks of the
 // launch, SPB = samples per block.
 // MB: partial slots per buffer, a compile-time bound >= NB for the sum
 // (slots NB..MB-1 hold zeros).
@@ -123,6 +123,7 @@ __host__ __device__ inline Layout layout(int dims, int nv, int M, int NB, int MB
   l.hist = o; o += 2 * 16 * NB * SPB;
   l.cm = o;  o += NB * 4 * ((M + 63) / 64);
   l.first = o; o += 2 * 256;
+  l.flag = o; o += 16;
   l.xs = o;  o += SPB * D4;
   l.mu = o;
   l.L = o + D4;
@@ -540,21 +541,36 @@ __device__ __forceinline__ int coef_of(int q, int r) { return r < 3 ? 3 * q + r 
 // remaining slots empty.  (16, 8), (8, 4), (32, 8), (32, 16) and (12, 6): a
 // 1000-sample 2D projection of 100 iterations took 179, 194, 183, 181 and
 // 186 us, a 20 x 100 plan 2.96, 2.95, 2.97, 3.04 and 2.94 ms.
-//
-// A search takes some hundred cycles per obstacle in reach, which a launch of
-// few iterations among many obstacles does not earn back: with more than three
-// obstacles per two iterations it looks kNearReach units far (124 obstacles, 76
-// iterations: a 10 x 76 plan of 18 problems 4820 us with 16 units, 4300 with 8;
-// 138 and 34: 966, 868; 113 and 60: 294, 255; but 69 and 29: 207, 223, and 37
-// and 35: 413, 435).
 #ifndef PRIEST_CULL_SLACK
 #define PRIEST_CULL_SLACK 0.25f
 #endif
 constexpr float kSlack = PRIEST_CULL_SLACK;
-constexpr float kReach = 16.0f, kRoomy = 8.0f, kNearReach = 8.0f;
+constexpr float kReach = 16.0f, kRoomy = 8.0f;
+
+// The first iterations, in which most items leave the reach of their search, and
+// tiles with crowded items run a loop without searches (plain_loop in
+// project_block).  Kernel time of 1000 samples, a 2D (3D) scene of 10 (20) m, us;
+// with no searching loop, with it alone, and with both:
+//   2D  60 obstacles,   6 iterations:  23.5, 28.9, 23.4;  100: 226, 181, 180
+//   2D 140,            12:  54, 60, 55;   25: 98, 90, 90;    100: 387, 252, 254
+//   2D 250,             6:  43, 80, 42;   25: 136, 210, 137; 100: 490, 665, 505
+//   2D 1000,          100: 1704, 2600, 1634
+//   3D  60,             6:  23, 26, 24;   25: 64, 61, 54;    100: 215, 164, 163
+//   3D 1000,           12: 110, 105, 104; 100: 676, 367, 356
+// With 2 or 6 plain iterations first, 60 obstacles and 12 iterations (2D) took
+// 39.5 and 36.3 us, 140 and 100 255 and 258.  At least kMinRanked iterations, and
+// as many as a block has near obstacles but kMostNear, must be left: with 180 and
+// 140 obstacles at 25 iterations 113 and 87 us for kMostNear = 3, 121 and 87 for
+// 4, 113 and 98 for 0.
+// The first look for crowded tiles in the searching loop comes after kBackFirst
+// iterations: 180 obstacles (2D), 25 and 100 iterations, 116 and 402 us, without
+// any 135 and 485; a 20 x 100 plan of 50 2.88 and 2.83 ms.  (After 2 and 4: 115
+// and 117 us, 2.89 ms.)  In 3D searching was the faster also with 1000.
+constexpr int kPlainFirst = 4, kMinRanked = 4, kMostNear = 3, kBackFirst = 8;
 
 // Obstacles an item keeps between iterations: its nearest ones, in registers.
-constexpr int lane_slots(int dims) { return dims == 2 ? 4 : 3; }
+// (3D: a third one spills registers, which alone takes 0.7 us a launch.)
+constexpr int lane_slots(int dims) { return dims == 2 ? 4 : 2; }
 
 // One 16-step time block of a wave of the time-split shapes: its items, and
 // the memory of its last obstacle search: every item's position at that time
@@ -568,7 +584,7 @@ struct TimeBlock {
   int t[NI];           // the items' steps
   float tt[NI];        // and times
   bool ok[NI];
-  float tmid[4];       // middle of the time window of each row of 16 lanes
+  int t0;              // the block's first step
   float pref[NI][DIMS], lim[NI];
   uint32_t nok;        // valid items (wave-uniform)
   uint32_t npairs;     // pairs of one evaluation (kept only while pairs are counted)
@@ -584,7 +600,7 @@ struct Scene {
   int M, K;
   float unit;    // kSlack * (smallest cull radius of the scene)
   float thalf;   // half the time window of a row of 16 lanes
-  float reach;   // of a search
+  float dt;      // time between steps
 };
 
 // Centre of obstacle j at item i's time (a static obstacle's comes unchanged).
@@ -657,6 +673,223 @@ __device__ __forceinline__ bool still_valid(const TimeBlock<NI, DIMS>& tb, const
   return __ballot(far) == 0ull;
 }
 
+// Box around the valid items of each row of 16 lanes (the items of 4 time steps).
+template <int DIMS, int NI>
+__device__ __forceinline__ void item_boxes(const TimeBlock<NI, DIMS>& tb, const float p[NI][DIMS],
+                                           float lo[DIMS][4], float hi[DIMS][4]) {
+#pragma unroll
+  for (int x = 0; x < DIMS; ++x) {
+    float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      mn = fminf(mn, tb.ok[i] ? p[i][x] : INFINITY);
+      mx = fmaxf(mx, tb.ok[i] ? p[i][x] : -INFINITY);
+    }
+    row_min4(mn, lo[x]);
+    row_max4(mx, hi[x]);
+  }
+}
+
+// Which obstacles of group g may come within `reach` of one of the boxes, and
+// which of those move.
+template <int DIMS, bool TRAJ, int NI>
+__device__ __forceinline__ void box_masks(const Scene& sc, const TimeBlock<NI, DIMS>& tb,
+                                          const float lo[DIMS][4], const float hi[DIMS][4], int g,
+                                          int lane, float reach, unsigned long long& mask,
+                                          unsigned long long& moving) {
+  const int M = sc.M;
+  // (lanes past the scene load the last record)
+  const int j = min(64 * g + lane, M - 1);
+  const float4 R0 = sc.rec[j], R1 = sc.rec[M + j];
+  bool cand = false;
+  // (the middles of the rows' time windows are worked out here rather than held
+  // over the iterations, which the copy sees to)
+  int t0 = tb.t0;
+  asm volatile("" : "+s"(t0));
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float tmid = sc.dt * (static_cast<float>(t0 + 4 * q) + 1.5f);
+    // (paths: the sphere around the whole path, grown by its radius)
+    const float oc[3] = {TRAJ ? R0.x : fmaf(R1.x, tmid, R0.x),
+                         TRAJ ? R0.y : fmaf(R1.y, tmid, R0.y),
+                         TRAJ ? R0.z : fmaf(R1.z, tmid, R0.z)};
+    float d2 = 0.0f;
+#pragma unroll
+    for (int x = 0; x < DIMS; ++x) {
+      const float e = fmaxf(fmaxf(lo[x][q] - oc[x], oc[x] - hi[x][q]), 0.0f);
+      d2 = fmaf(e, e, d2);
+    }
+    const float rr = TRAJ ? R0.w + reach + R1.x : fmaf(R1.w, sc.thalf, R0.w + reach);
+    cand = cand || (d2 < rr * rr);
+  }
+  cand = cand && 64 * g + lane < M;
+  mask = __ballot(cand);
+  moving = __ballot(cand && !TRAJ && R1.w != 0.0f);
+}
+
+// The obstacles that may come within one unit of some item of a time block:
+// masks (all, moving ones) of the first kRegGroups groups of 64 in scalar
+// registers, those of further groups in LDS.
+constexpr int kRegGroups = 2;
+struct NearMasks {
+  unsigned long long cm[kRegGroups], mv[kRegGroups];
+  uint32_t n;
+};
+
+template <int DIMS, bool TRAJ, int NI>
+__device__ __forceinline__ void near_obstacles(const Scene& sc, TimeBlock<NI, DIMS>& tb,
+                                               const float p[NI][DIMS], int lane, uint32_t* wm,
+                                               NearMasks& nm) {
+  float lo[DIMS][4], hi[DIMS][4];
+  item_boxes<DIMS, NI>(tb, p, lo, hi);
+  nm.n = 0;
+#pragma unroll
+  for (int g = 0; g < kRegGroups; ++g) {
+    nm.cm[g] = nm.mv[g] = 0ull;
+    if (64 * g < sc.M) box_masks<DIMS, TRAJ, NI>(sc, tb, lo, hi, g, lane, sc.unit, nm.cm[g], nm.mv[g]);
+    nm.n += static_cast<uint32_t>(__builtin_popcountll(nm.cm[g]));
+  }
+#pragma unroll 1
+  for (int g = kRegGroups; 64 * g < sc.M; ++g) {
+    unsigned long long m, mv;
+    box_masks<DIMS, TRAJ, NI>(sc, tb, lo, hi, g, lane, sc.unit, m, mv);
+    nm.n += static_cast<uint32_t>(__builtin_popcountll(m));
+    if (lane == 0)
+      *reinterpret_cast<uint4*>(wm + 4 * g) =
+          make_uint4(static_cast<uint32_t>(m), static_cast<uint32_t>(m >> 32),
+                     static_cast<uint32_t>(mv), static_cast<uint32_t>(mv >> 32));
+  }
+  if (sc.M > 64 * kRegGroups) wave_lds_sync();
+  tb.npairs = nm.n * tb.nok;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    tb.lim[i] = sc.unit;
+#pragma unroll
+    for (int x = 0; x < DIMS; ++x) tb.pref[i][x] = p[i][x];
+  }
+}
+
+// Calls fn(first obstacle of the group, mask, moving ones) for every group with
+// a near obstacle.
+template <typename F>
+__device__ __forceinline__ void near_groups(int M, const NearMasks& nm, const uint32_t* wm, F fn) {
+  if (nm.n == 0) return;  // (or a block without a valid item, whose masks were never made)
+#pragma unroll 1
+  for (int g = 0; 64 * g < M; ++g) {
+    unsigned long long m = g == 0 ? nm.cm[0] : nm.cm[1], mv = g == 0 ? nm.mv[0] : nm.mv[1];
+    if (g >= kRegGroups) {
+      const uint4 m4 = *reinterpret_cast<const uint4*>(wm + 4 * g);
+      // (readfirstlane returns int: widen through uint32_t, not sign-extended)
+      auto u64 = [](uint32_t lo, uint32_t hi) {
+        return static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lo))) |
+               (static_cast<unsigned long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(hi)))
+                << 32);
+      };
+      m = u64(m4.x, m4.y);
+      mv = u64(m4.z, m4.w);
+    }
+    if (m) fn(64 * g, m, mv);
+  }
+}
+
+// Whether some item has more than L obstacles within one unit.
+template <int DIMS, bool TRAJ, int NI>
+__device__ __forceinline__ bool crowded(const Scene& sc, const TimeBlock<NI, DIMS>& tb,
+                                        const float p[NI][DIMS], int lane, const uint32_t* wm,
+                                        const NearMasks& nm) {
+  constexpr int L = TimeBlock<NI, DIMS>::L;
+  if (nm.n <= static_cast<uint32_t>(L)) return false;
+  int n[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) n[i] = 0;
+  near_groups(sc.M, nm, wm, [&](int base, unsigned long long m, unsigned long long) {
+    while (m) {
+      const int j = base + __builtin_ctzll(m);
+      m &= m - 1;
+      const float4 R0 = sc.rec[j], R1 = sc.rec[sc.M + j];
+      const float c[3] = {R0.x, R0.y, R0.z}, v[3] = {R1.x, R1.y, R1.z};
+      const float rr = R0.w + sc.unit;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        float oc[DIMS], d2 = 0.0f;
+        centre_at<DIMS, TRAJ>(sc, tb, i, j, c, v, oc);
+#pragma unroll
+        for (int x = 0; x < DIMS; ++x) {
+          const float e = p[i][x] - oc[x];
+          d2 = fmaf(e, e, d2);
+        }
+        n[i] += d2 < rr * rr ? 1 : 0;
+      }
+    }
+  });
+  bool any = false;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) any = any || (tb.ok[i] && n[i] > L);
+  return __ballot(any) != 0ull;
+}
+
+// Obstacle push-outs of one time block's items, every near obstacle for every
+// item, in the canonical order, two at a time (their offsets and factors are
+// independent).
+template <int DIMS, bool LAST, bool ACC, bool TRAJ, int NI>
+__device__ __forceinline__ void near_pushes(const Scene& sc, const TimeBlock<NI, DIMS>& tb,
+                                            const float p[NI][DIMS], float S[NI][DIMS], float r2[NI],
+                                            int lane, const uint32_t* wm, const NearMasks& nm) {
+  near_groups(sc.M, nm, wm, [&](int base, unsigned long long cmask, unsigned long long mvmask) {
+    const int l = min(base + lane, sc.M - 1);
+    const float4 R0 = sc.rec[l], R1 = sc.rec[sc.M + l], R2 = sc.rec[2 * sc.M + l];
+    auto run = [&](unsigned long long m, auto moving_tag) {
+      constexpr bool MV = decltype(moving_tag)::value;
+      // (paths: the centre at each item's own step)
+      auto term = [&](const Rec& o, int j, int i) {
+        if constexpr (TRAJ) {
+          float oc[DIMS];
+          centre_at<DIMS, TRAJ>(sc, tb, i, j, nullptr, nullptr, oc);
+          Rec t = o;
+          t.cx = oc[0];
+          t.cy = oc[1];
+          if constexpr (DIMS == 3) t.cz = oc[DIMS - 1];
+          return pair_term<DIMS, LAST, false>(t, tb.tt[i], p[i]);
+        } else {
+          return pair_term<DIMS, LAST, MV>(o, tb.tt[i], p[i]);
+        }
+      };
+      while (m) {
+        const int b0 = __builtin_ctzll(m);
+        m &= m - 1;
+        const Rec o0 = rec_of_lane<DIMS, MV>(R0, R1, R2, b0);
+        if (DIMS == 2 && m) {
+          const int b1 = __builtin_ctzll(m);
+          m &= m - 1;
+          const Rec o1 = rec_of_lane<DIMS, MV>(R0, R1, R2, b1);
+          PairTerm<DIMS> t0[NI], t1[NI];
+#pragma unroll
+          for (int i = 0; i < NI; ++i) t0[i] = term(o0, base + b0, i);
+#pragma unroll
+          for (int i = 0; i < NI; ++i) t1[i] = term(o1, base + b1, i);
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            pair_add<DIMS, ACC>(o0, t0[i], S[i], r2[i]);
+            pair_add<DIMS, ACC>(o1, t1[i], S[i], r2[i]);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < NI; ++i) pair_add<DIMS, ACC>(o0, term(o0, base + b0, i), S[i], r2[i]);
+        }
+      }
+    };
+    run(cmask & ~mvmask, std::false_type{});
+    if constexpr (!TRAJ) run(mvmask, std::true_type{});
+  });
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+    if (!tb.ok[i]) {
+#pragma unroll
+      for (int x = 0; x < DIMS; ++x) S[i][x] = 0.0f;
+      r2[i] = 0.0f;
+    }
+}
+
 // Obstacle search of one time block.
 //
 // First the obstacles that may come near the boxes around the items, one box
@@ -674,43 +907,14 @@ __device__ __forceinline__ void search_obstacles(const Scene& sc, TimeBlock<NI, 
                                                  bool count) {
   constexpr int L = TimeBlock<NI, DIMS>::L;
   const int M = sc.M;
-  const float reach = sc.reach;
+  const float reach = sc.unit * kReach;
   float lo[DIMS][4], hi[DIMS][4];
-#pragma unroll
-  for (int x = 0; x < DIMS; ++x) {
-    float mn = INFINITY, mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      mn = fminf(mn, tb.ok[i] ? p[i][x] : INFINITY);
-      mx = fmaxf(mx, tb.ok[i] ? p[i][x] : -INFINITY);
-    }
-    row_min4(mn, lo[x]);
-    row_max4(mx, hi[x]);
-  }
+  item_boxes<DIMS, NI>(tb, p, lo, hi);
   uint32_t ncand = 0;
 #pragma unroll 1
   for (int g = 0; 64 * g < M; ++g) {
-    // (lanes past the scene load the last record)
-    const int j = min(64 * g + lane, M - 1);
-    const float4 R0 = sc.rec[j], R1 = sc.rec[M + j];
-    bool cand = false;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      // (paths: the sphere around the whole path, grown by its radius)
-      const float oc[3] = {TRAJ ? R0.x : fmaf(R1.x, tb.tmid[q], R0.x),
-                           TRAJ ? R0.y : fmaf(R1.y, tb.tmid[q], R0.y),
-                           TRAJ ? R0.z : fmaf(R1.z, tb.tmid[q], R0.z)};
-      float d2 = 0.0f;
-#pragma unroll
-      for (int x = 0; x < DIMS; ++x) {
-        const float e = fmaxf(fmaxf(lo[x][q] - oc[x], oc[x] - hi[x][q]), 0.0f);
-        d2 = fmaf(e, e, d2);
-      }
-      const float rr = TRAJ ? R0.w + reach + R1.x : fmaf(R1.w, sc.thalf, R0.w + reach);
-      cand = cand || (d2 < rr * rr);
-    }
-    cand = cand && 64 * g + lane < M;
-    const unsigned long long mask = __ballot(cand), moving = __ballot(cand && !TRAJ && R1.w != 0.0f);
+    unsigned long long mask, moving;
+    box_masks<DIMS, TRAJ, NI>(sc, tb, lo, hi, g, lane, reach, mask, moving);
     ncand += static_cast<uint32_t>(__builtin_popcountll(mask));
     if (lane == 0)
       *reinterpret_cast<uint4*>(wm + 4 * g) =
@@ -990,6 +1194,20 @@ __device__ __forceinline__ float affine_row(float x, const float* L, const float
   return x;
 }
 
+// The launch's arguments in constant memory.  What only the end of a tile needs
+// is read through a copy of this pointer that the compiler cannot see through
+// (`late`), so that it is loaded there instead of being held in scalar registers
+// over the iterations.
+using ConstArgs = const __attribute__((address_space(4))) ProjArgs*;
+// (the first argument of a kernel that takes them by value)
+__device__ __forceinline__ ConstArgs kernel_args() {
+  return (ConstArgs)__builtin_amdgcn_kernarg_segment_ptr();
+}
+__device__ __forceinline__ ConstArgs late(ConstArgs p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // One block's work: whole projections of tiles first, first + stride, ...
 // below `total` (LOOP), or of tile `first` only; tile t holds samples
 // [SPB*j, SPB*j + SPB) of problem t / blocks_per_problem, j its index within
@@ -1000,7 +1218,8 @@ __device__ __forceinline__ float affine_row(float x, const float* L, const float
 // bound; C3: there may be more than 12 coefficients per axis.
 template <int DIMS, int AS, int RT, int MAXT, bool BF16, bool LOOP, bool HIST = false,
           bool TRAJ = false, bool C3 = true>
-__device__ __forceinline__ void project_block(const ProjArgs& a, int first, int stride, int total) {
+__device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args, int first, int stride,
+                                              int total) {
   static_assert(AS == 4 || AS == 8 || (AS == 2 && DIMS == 2), "2 axis slots only hold 2D samples");
   constexpr int SPB = 16 / AS;           // samples per block
   // items per lane per time block; with 8 slots per sample only the lanes of
@@ -1010,7 +1229,8 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
   constexpr int NR = C3 ? 4 : 3;         // coefficient chunks
   extern __shared__ float4 sm4[];
   float* sm = reinterpret_cast<float*>(sm4);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, TW = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int TW = blockDim.x >> 6;
   const int NB = TW * RT;
   const int nv = a.nv, K = a.K, M = a.M, D = DIMS * nv, D4 = round4(D);
   const Layout l = layout(DIMS, nv, M, NB, MB, SPB, a.mode);
@@ -1036,10 +1256,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       blk[rt].t[i] = t0 + 4 * q + NI * cx + i;
       blk[rt].tt[i] = a.dt * static_cast<float>(blk[rt].t[i]);
     }
-    // time window of each row of 16 lanes: steps t0 + 4 q + 0..3
-#pragma unroll
-    for (int qq = 0; qq < 4; ++qq)
-      blk[rt].tmid[qq] = a.dt * (static_cast<float>(t0 + 4 * qq) + 1.5f);
+    blk[rt].t0 = t0;
   }
   float4* rec = reinterpret_cast<float4*>(sm + l.rec);
   float* xs = sm + l.xs;
@@ -1056,39 +1273,53 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       for (int r = 0; r < 4; ++r) {
         const int t0 = 16 * (w + TW * rt);
         const int tf = t0 + col, cf = coef_of(q, r);
-        const float wf = a.W[(min(tf, K - 1) * 3 + d) * nv + min(cf, nv - 1)];
-        Af[rt][d][r] = (tf < K && cf < nv) ? wf : 0.0f;
+        Af[rt][d][r] = a.W[(min(tf, K - 1) * 3 + d) * nv + min(cf, nv - 1)];
         const int tb = t0 + 4 * q + r, cb = coef_of(col >> 2, col & 3);
-        const float wb = a.W[(min(tb, K - 1) * 3 + d) * nv + min(cb, nv - 1)];
-        Ab[rt][d][r] = (tb < K && cb < nv) ? wb : 0.0f;
+        Ab[rt][d][r] = a.W[(min(tb, K - 1) * 3 + d) * nv + min(cb, nv - 1)];
       }
   // (Pi and c0 = M12 b enter the first iteration only: they wait in LDS)
   float* first_op = sm + l.first + lane * 4;
   const int crow = coef_of(col >> 2, col & 3);
+  float Ap[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int ck = coef_of(q, r);
-    const bool ok = (crow < nv) && (ck < nv);
-    const int at = min(crow, nv - 1) * nv + min(ck, nv - 1);
-    const float m = a.M11[at], pi = a.Pi[at];
-    Am[r] = ok ? m : 0.0f;
-    if (w == 0) first_op[r] = ok ? pi : 0.0f;
+    const int at = min(crow, nv - 1) * nv + min(coef_of(q, r), nv - 1);
+    Am[r] = a.M11[at];
+    Ap[r] = w == 0 ? a.Pi[at] : 0.0f;
   }
   const bool chunk3 = C3 && nv > 12;  // slot r = 3 holds coefficients 12..15
   const float rho = a.rho;
   f4 xb;
   // mixed precision: W^T rows as BF16, M11 as a BF16 hi/lo pair
   s4 Abf[RT][3], Mhi, Mlo;
-  if constexpr (BF16) {
+  // (zeros past the horizon and the coefficients)
+  auto pad_operands = [&] {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int r = 0; r < 4; ++r) {
+      const int ck = coef_of(q, r);
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
-        Abf[rt][d] = pack_bf16(Ab[rt][d][0], Ab[rt][d][1], Ab[rt][d][2], Ab[rt][d][3]);
-    Mhi = pack_bf16(Am[0], Am[1], Am[2], Am[3]);
-    Mlo = pack_bf16(Am[0] - from_bf16(Mhi[0]), Am[1] - from_bf16(Mhi[1]),
-                    Am[2] - from_bf16(Mhi[2]), Am[3] - from_bf16(Mhi[3]));
-  }
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const int t0 = 16 * (w + TW * rt);
+          if (t0 + col >= K || ck >= nv) Af[rt][d][r] = 0.0f;
+          if (t0 + 4 * q + r >= K || crow >= nv) Ab[rt][d][r] = 0.0f;
+        }
+      if (crow >= nv || ck >= nv) Am[r] = Ap[r] = 0.0f;
+    }
+    if constexpr (BF16) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+          Abf[rt][d] = pack_bf16(Ab[rt][d][0], Ab[rt][d][1], Ab[rt][d][2], Ab[rt][d][3]);
+      Mhi = pack_bf16(Am[0], Am[1], Am[2], Am[3]);
+      Mlo = pack_bf16(Am[0] - from_bf16(Mhi[0]), Am[1] - from_bf16(Mhi[1]),
+                      Am[2] - from_bf16(Mhi[2]), Am[3] - from_bf16(Mhi[3]));
+    }
+    if (w == 0) *reinterpret_cast<float4*>(first_op) = make_float4(Ap[0], Ap[1], Ap[2], Ap[3]);
+  };
+  bool padded = false;
   const int mask_words = 4 * ((M + 63) / 64);
   uint32_t* wm0 = reinterpret_cast<uint32_t*>(sm + l.cm) + w * RT * mask_words;
 
@@ -1120,6 +1351,16 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
     const int s0 = (t - prob * a.blocks_per_problem) * SPB;
     const int ns = min(SPB, a.N - s0);
     const float* bc = a.bc + prob * a.bc_stride;
+    // (the first wave's, for the first iteration: loaded before anything waits)
+    float m12[4][6], bv[6];
+    if (w == 0) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        bv[i] = bc[min(cx, DIMS - 1) * 6 + i];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m12[r][i] = a.M12[min(coef_of(q, r), nv - 1) * 6 + i];
+      }
+    }
     // ---- scene records, samples ---------------------------------------------
     // (every reader of the previous tile's records passed the barrier that
     // precedes its epilogue)
@@ -1169,10 +1410,12 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
         float s = 0.0f;
 #pragma unroll
         for (int i = 0; i < 6; ++i)
-          s = fmaf(a.M12[min(c, nv - 1) * 6 + i], bc[min(cx, DIMS - 1) * 6 + i], s);
+          s = fmaf(m12[r][i], bv[i], s);
         first_op[256 + r] = (cx < DIMS && cs < ns && c < nv) ? s : 0.0f;
       }
     }
+    if (!padded) pad_operands();
+    padded = true;
     __syncthreads();
 
     const bool colok = (cx < DIMS) && (cs < ns);
@@ -1184,12 +1427,11 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
     }
     xb = xi;
     f4 lam = {0.0f, 0.0f, 0.0f, 0.0f};
-    Scene sc{rec, a.obs + prob * a.obs_stride, M, K, 0.0f, a.dt * 1.5f, 0.0f};
+    Scene sc{rec, a.obs + prob * a.obs_stride, M, K, 0.0f, a.dt * 1.5f, a.dt};
     {
       float cmin = INFINITY;
       for (int j = lane; j < M; j += 64) cmin = fminf(cmin, rec[j].w);
       sc.unit = kSlack * wave_min(cmin);
-      sc.reach = sc.unit * (2 * M > 3 * a.n_iter ? kNearReach : kReach);
     }
     uint32_t pairs = 0;
     // Budgets (per lane, in units of max|Delta xi_bar| of the lane's sample):
@@ -1199,13 +1441,8 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
     // every lane of the wave has budget left, that row type's push-outs are
     // exactly zero and its rows are not evaluated.
     float Bp[RT], Bv[RT], Ba[RT], X;
-    bool needP[RT], needV[RT], needA[RT], any_ok[RT];
-    {
-      float m = 0.0f;
-#pragma unroll
-      for (int r = 0; r < NR; ++r) m = fmaxf(m, fabsf(xi[r]));
-      X = quad_max(m) * 1.000002f;
-    }
+    uint32_t need = 0;  // bits 3 rt + 0, 1, 2: positions, velocities, accelerations of block rt
+    bool any_ok[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       TimeBlock<NI, DIMS>& b = blk[rt];
@@ -1222,8 +1459,6 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
 #pragma unroll
         for (int x = 0; x < DIMS; ++x) b.pref[i][x] = 0.0f;
       }
-      Bp[rt] = Bv[rt] = Ba[rt] = -1.0f;
-      needP[rt] = needV[rt] = needA[rt] = true;
     }
     const float pscale = a.bscale[0] * (DIMS == 3 ? 0.57735026f : 0.70710678f);
     auto budget = [&](float m) { return fmaf(m, 0.99899f, -1.0e-5f * X); };
@@ -1240,161 +1475,69 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       else if (pr == 1) __builtin_amdgcn_s_setprio(1);
       else __builtin_amdgcn_s_setprio(0);
     }
-    // (the position rows are evaluated as soon as an iterate is there, beside
-    // the reductions of its budgets)
-    f4 YP[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) YP[rt] = chain(rt, 0);
     // bit 2 rt + b: this block's partials in buffer b may be other than zero
     uint32_t dirty = ~0u;
-    // ---- projection iterations ---------------------------------------------------
-    for (int k = 0;; ++k) {
-      // positions, and the obstacle search where they have left the reach of
-      // the last one (one more time after the last iteration, for the residual)
-      const bool last = k == a.n_iter;
-      float p[RT][NI][DIMS];
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-        if (needP[rt] || last) {
-          quad_items(YP[rt], lane, p[rt]);
-          if (__builtin_expect(!still_valid<DIMS>(blk[rt], p[rt]), 0))
-            search_obstacles<DIMS, TRAJ>(sc, blk[rt], p[rt], lane, wm0 + rt * mask_words,
-                                         a.pair_count != nullptr);
-        }
-      if (last) break;
-      const f4 zb = {0.0f, 0.0f, 0.0f, 0.0f};
-      const bool lowp = BF16 && (k < a.bf16_iters);
+    const f4 zb = {0.0f, 0.0f, 0.0f, 0.0f};
+    // One iteration's right-hand side of one block, from the push-outs of the
+    // row types in nz (the others have none).
+    auto block_rhs = [&](int rt, int k, bool lowp, uint32_t nz, const float (&S)[NI][DIMS],
+                         const float (&dv)[NI][DIMS], const float (&da)[NI][DIMS],
+                         const float (&r2)[NI]) __attribute__((always_inline)) {
+      [[maybe_unused]] const TimeBlock<NI, DIMS>& b = blk[rt];
       float* gp = sm + l.gp + (k & 1) * NP * 256;
+      if constexpr (HIST) {
+        // squared push-outs of this iteration per (t, sample), summed per
+        // sample after the barrier below (double-buffered by iteration)
+        float* hb = sm + l.hist + (k & 1) * 16 * NB * SPB;
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        TimeBlock<NI, DIMS>& b = blk[rt];
-        // push-outs of the row types that may push; nz: those with a nonzero
-        // push-out on some item of the block (the others are left out of the
-        // right-hand side: adding exact zeros to an accumulator that starts
-        // at +0 changes nothing)
-        uint32_t nz = 0;
-        float S[NI][DIMS], dv[NI][DIMS], da[NI][DIMS], r2[NI];
-#pragma unroll
-        for (int n = 0; n < NI; ++n) r2[n] = 0.0f;
-        f4 YV, YA;
-        if (needV[rt]) YV = chain(rt, 1);
-        if (needA[rt]) YA = chain(rt, 2);
-        if (needP[rt]) {
-#pragma unroll
-          for (int n = 0; n < NI; ++n)
-#pragma unroll
-            for (int x = 0; x < DIMS; ++x) S[n][x] = 0.0f;
-          obstacle_pushes<DIMS, false, HIST, TRAJ>(sc, b, p[rt], S, r2, lane, wm0 + rt * mask_words);
-          pairs += b.npairs;
-          if (a.box.on) {
-#pragma unroll
-            for (int n = 0; n < NI; ++n)
-              if (b.ok[n]) box_push<DIMS>(a.box, p[rt][n], S[n], r2[n]);
-          } else if (b.depth == 0) {
-            float left = INFINITY;
-#pragma unroll
-            for (int n = 0; n < NI; ++n) {
-              float d2 = 0.0f;
-#pragma unroll
-              for (int x = 0; x < DIMS; ++x) {
-                const float e = p[rt][n][x] - b.pref[n][x];
-                d2 = fmaf(e, e, d2);
-              }
-              left = b.ok[n] ? fminf(left, b.lim[n] - __builtin_amdgcn_sqrtf(d2) * 1.000001f) : left;
-            }
-            Bp[rt] = any_ok[rt] ? budget(left * pscale) : INFINITY;
-          }
-          bool any = false;
-#pragma unroll
-          for (int n = 0; n < NI; ++n)
-#pragma unroll
-            for (int x = 0; x < DIMS; ++x) any = any || (S[n][x] != 0.0f);
-          nz = __ballot(any) != 0ull ? 1u : 0u;
-        }
-        // velocity / acceleration bounds
-        auto bounds = [&](const f4& Y, float wmax, float scale, float (&d)[NI][DIMS], float& B,
-                          uint32_t bit) {
-          float wv[NI][DIMS];
-          quad_items(Y, lane, wv);
-          float m = 0.0f;
-          bool over = false;
-          const float wcap = fminf(wmax * wmax, 3.402823466e38f);  // (an infinite |w|^2 is over any bound)
-#pragma unroll
-          for (int n = 0; n < NI; ++n) {
-            float ww = 0.0f;
-#pragma unroll
-            for (int x = 0; x < DIMS; ++x) ww = fmaf(wv[n][x], wv[n][x], ww);
-            over = over || (b.ok[n] && !(ww <= wcap));
-            m = b.ok[n] ? fmaxf(m, ww) : m;
-          }
-          if (__ballot(over) != 0ull) {
-            nz |= bit;
-            B = -1.0f;
-#pragma unroll
-            for (int n = 0; n < NI; ++n) {
-#pragma unroll
-              for (int x = 0; x < DIMS; ++x) d[n][x] = 0.0f;
-              if (b.ok[n]) bound_push<DIMS>(wv[n], wmax, d[n], r2[n]);
-            }
-          } else {
-            // (v_sqrt_f32 is within 1 ulp)
-            B = any_ok[rt] ? budget((wmax * 0.999999f - __builtin_amdgcn_sqrtf(m) * 1.000001f) * scale)
-                           : INFINITY;
-          }
-        };
-        if (needV[rt]) bounds(YV, a.vmax, a.bscale[1], dv, Bv[rt], 2u);
-        if (needA[rt]) bounds(YA, a.amax, a.bscale[2], da, Ba[rt], 4u);
-        if constexpr (HIST) {
-          // squared push-outs of this iteration per (t, sample), summed per
-          // sample after the barrier below (double-buffered by iteration)
-          float* hb = sm + l.hist + (k & 1) * 16 * NB * SPB;
-#pragma unroll
-          for (int n = 0; n < NI; ++n)
-            if (AS <= 4 || cx < 4) hb[b.t[n] * SPB + cs] = b.ok[n] ? r2[n] : 0.0f;
-        }
-        // right-hand side of this block
-        const uint32_t db = 1u << (2 * rt + (k & 1));
-        if (nz || (dirty & db)) {
-          f4 part;
-          if (lowp) {
-            // BF16 operands, FP32 accumulation: one K = 16 MFMA per row type
-            // covers a whole 16-step block
-            part = zb;
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-              if (nz & (1u << d)) {
-                const f4 B = quad_cols(d == 0 ? S : d == 1 ? dv : da, lane);
-                part = mfma_bf16(Abf[rt][d], pack_bf16(B[0], B[1], B[2], B[3]), part);
-              }
-          } else {
-            // two accumulation chains over the three row types and four
-            // k-chunks, added once at the end: one chain is faster for a lone
-            // small launch, but its dependent products stall full launches
-            // (N = 64000: 8.2 against 6.0 ms)
-            f4 acc0 = zb, acc1 = zb;
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-              if (nz & (1u << d)) {
-                const f4 B = quad_cols(d == 0 ? S : d == 1 ? dv : da, lane);
-                acc0 = mfma(Ab[rt][d][0], B[0], acc0);
-                acc1 = mfma(Ab[rt][d][1], B[1], acc1);
-                acc0 = mfma(Ab[rt][d][2], B[2], acc0);
-                acc1 = mfma(Ab[rt][d][3], B[3], acc1);
-              }
-            part = acc0 + acc1;
-          }
-          const int tb = w + TW * rt;
-          float* slot = gp + (HALF && tb >= NP ? tb - NP : tb) * 256 + lane + (HALF && tb >= NP ? 2 : 0);
-          if (!HALF || !(lane & 2)) {
-            slot[0] = part[0];
-            slot[64] = part[1];
-            slot[128] = part[2];
-            if (chunk3) slot[192] = part[3];
-          }
-          dirty = (dirty & ~db) | (nz ? db : 0u);
-        }
+        for (int n = 0; n < NI; ++n)
+          if (AS <= 4 || cx < 4) hb[b.t[n] * SPB + cs] = b.ok[n] ? r2[n] : 0.0f;
       }
-      __syncthreads();
+      // right-hand side of this block
+      const uint32_t db = 1u << (2 * rt + (k & 1));
+      if (nz || (dirty & db)) {
+        f4 part;
+        if (lowp) {
+          // BF16 operands, FP32 accumulation: one K = 16 MFMA per row type
+          // covers a whole 16-step block
+          part = zb;
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            if (nz & (1u << d)) {
+              const f4 B = quad_cols(d == 0 ? S : d == 1 ? dv : da, lane);
+              part = mfma_bf16(Abf[rt][d], pack_bf16(B[0], B[1], B[2], B[3]), part);
+            }
+        } else {
+          // two accumulation chains over the three row types and four
+          // k-chunks, added once at the end: one chain is faster for a lone
+          // small launch, but its dependent products stall full launches
+          // (N = 64000: 8.2 against 6.0 ms)
+          f4 acc0 = zb, acc1 = zb;
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            if (nz & (1u << d)) {
+              const f4 B = quad_cols(d == 0 ? S : d == 1 ? dv : da, lane);
+              acc0 = mfma(Ab[rt][d][0], B[0], acc0);
+              acc1 = mfma(Ab[rt][d][1], B[1], acc1);
+              acc0 = mfma(Ab[rt][d][2], B[2], acc0);
+              acc1 = mfma(Ab[rt][d][3], B[3], acc1);
+            }
+          part = acc0 + acc1;
+        }
+        const int tb = w + TW * rt;
+        float* slot = gp + (HALF && tb >= NP ? tb - NP : tb) * 256 + lane + (HALF && tb >= NP ? 2 : 0);
+        if (!HALF || !(lane & 2)) {
+          slot[0] = part[0];
+          slot[64] = part[1];
+          slot[128] = part[2];
+          if (chunk3) slot[192] = part[3];
+        }
+        dirty = (dirty & ~db) | (nz ? db : 0u);
+      }
+    };
+    // The sum over the blocks, multiplier update and QP step.
+    auto iterate = [&](int k, bool lowp, auto first_tag) __attribute__((always_inline)) {
+      const float* gp = sm + l.gp + (k & 1) * NP * 256;
       // g = +0 + the block partials added one by one in time-block order
       // (slots NB..MB-1 hold +0, which leaves the sum unchanged).  No partial
       // is -0 (its MFMA chains start at +0), so neither is any sum, and a
@@ -1455,8 +1598,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
       }
 #pragma unroll
       for (int r = 0; r < NR; ++r) lam[r] += rho * g[r];
-      const f4 xold = xb;
-      if (k == 0) {
+      if (decltype(first_tag)::value && k == 0) {
         const f4 Ap = *reinterpret_cast<const f4*>(first_op);
         const f4 c0v = *reinterpret_cast<const f4*>(first_op + 256);
         const f4 u = lam + rho * g;
@@ -1486,115 +1628,366 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int first, int 
         xb = mfma(Am[2], u[2], mfma(Am[1], u[1], mfma(Am[0], u[0], xb)));
         if (chunk3) xb = mfma(Am[3], u[3], xb);
       }
+    };
+    // Whether any wave's word is set: the same answer in every wave.  The words
+    // are written again only iterations (with their barriers) later.
+    int* flag = reinterpret_cast<int*>(sm + l.flag);
+    auto any_wave = [&](bool mine) {
+      if (lane == 0) flag[w] = mine;
+      __syncthreads();
+      return __ballot(lane < TW && flag[min(lane, TW - 1)] != 0) != 0ull;
+    };
+    const int ahead = max(a.n_iter, a.trial_of);
+    NearMasks nm[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) nm[rt] = NearMasks{};
+    // Iterations from k without search or budgets: every block's near obstacles
+    // for all its items, and every row type, in each.  Returns the iteration it
+    // stopped at: the last, or (choose) the first the searching loop is to do.
+    auto plain_loop = [&](int k, auto choose) __attribute__((always_inline)) {
+      constexpr bool CHOOSE = decltype(choose)::value;
+      int stay = kPlainFirst, next = a.n_iter - kPlainFirst < kMinRanked ? a.n_iter : kPlainFirst;
+      while (k < a.n_iter) {
+        const bool lowp = BF16 && (k < a.bf16_iters);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          TimeBlock<NI, DIMS>& b = blk[rt];
+          // (the three chains interleave, so each product waits on nothing)
+          f4 Y[3];
+#pragma unroll
+          for (int d = 0; d < 3; ++d) Y[d] = mfma(Af[rt][d][0], xb[0], zb);
+#pragma unroll
+          for (int c = 1; c < 3; ++c)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) Y[d] = mfma(Af[rt][d][c], xb[c], Y[d]);
+          if (chunk3) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) Y[d] = mfma(Af[rt][d][3], xb[3], Y[d]);
+          }
+          float p[NI][DIMS], v[NI][DIMS], ac[NI][DIMS], S[NI][DIMS], dv[NI][DIMS], da[NI][DIMS], r2[NI];
+          quad_items(Y[0], lane, p);
+          quad_items(Y[1], lane, v);
+          quad_items(Y[2], lane, ac);
+#pragma unroll
+          for (int n = 0; n < NI; ++n) {
+            r2[n] = 0.0f;
+#pragma unroll
+            for (int x = 0; x < DIMS; ++x) S[n][x] = dv[n][x] = da[n][x] = 0.0f;
+          }
+          uint32_t* wm = wm0 + rt * mask_words;
+          if (!still_valid<DIMS>(b, p)) near_obstacles<DIMS, TRAJ>(sc, b, p, lane, wm, nm[rt]);
+          near_pushes<DIMS, false, HIST, TRAJ>(sc, b, p, S, r2, lane, wm, nm[rt]);
+          pairs += b.npairs;
+#pragma unroll
+          for (int n = 0; n < NI; ++n)
+            if (b.ok[n]) {
+              if (a.box.on) box_push<DIMS>(a.box, p[n], S[n], r2[n]);
+              bound_push<DIMS>(v[n], a.vmax, dv[n], r2[n]);
+              bound_push<DIMS>(ac[n], a.amax, da[n], r2[n]);
+            }
+          block_rhs(rt, k, lowp, 7u, S, dv, da, r2);
+        }
+        __syncthreads();
+        if constexpr (CHOOSE) iterate(k, lowp, std::true_type{});
+        else iterate(k, lowp, std::false_type{});
+        ++k;
+        if constexpr (CHOOSE)
+          if (k == next && k < a.n_iter) {
+            bool crowd = false;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+              float p[NI][DIMS];
+              quad_items(chain(rt, 0), lane, p);
+              uint32_t* wm = wm0 + rt * mask_words;
+              if (!still_valid<DIMS>(blk[rt], p)) near_obstacles<DIMS, TRAJ>(sc, blk[rt], p, lane, wm, nm[rt]);
+              crowd = crowd || static_cast<int>(nm[rt].n) > ahead - k + kMostNear ||
+                      crowded<DIMS, TRAJ>(sc, blk[rt], p, lane, wm, nm[rt]);
+            }
+            if (!any_wave(crowd)) break;
+            stay *= 2;
+            next = a.n_iter - k - stay < kMinRanked ? a.n_iter : k + stay;
+          }
+      }
+      return k;
+    };
+    // ---- projection iterations ---------------------------------------------------
+    // The plain loop first (kPlainFirst), then the searching one, unless an item
+    // is crowded, or what is left would not earn the search of the block with the
+    // most near obstacles; then the question is put again after twice as many
+    // iterations.  In 2D a tile found crowded after kBackFirst, twice as many, ...
+    // searching iterations ends in the plain loop.
+    f4 YP[RT];
+    bool plain = true;
+    int k0 = plain_loop(0, std::true_type{});
+    if (k0 < a.n_iter) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) YP[rt] = chain(rt, 0);
-      // the budgets of a sample shrink by its largest coefficient change
-      // (rounded up)
-      float m = 0.0f;
+      {
+        float m = 0.0f;
 #pragma unroll
-      for (int r = 0; r < NR; ++r) m = fmaxf(m, fabsf(xb[r] - xold[r]));
-      const float dl = quad_max(m) * 1.000002f;
-      X += dl;
+        for (int r = 0; r < NR; ++r) m = fmaxf(m, fabsf(xb[r]));
+        X = quad_max(m) * 1.000002f;
+      }
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        Bp[rt] -= dl;
-        Bv[rt] -= dl;
-        Ba[rt] -= dl;
-        needP[rt] = __ballot(!(Bp[rt] >= 0.0f)) != 0ull;
-        needV[rt] = __ballot(!(Bv[rt] >= 0.0f)) != 0ull;
-        needA[rt] = __ballot(!(Ba[rt] >= 0.0f)) != 0ull;
+        need |= 7u << (3 * rt);
+        Bp[rt] = Bv[rt] = Ba[rt] = -1.0f;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) blk[rt].lim[i] = -1.0f;
+      }
+      int stay = kBackFirst, stop = DIMS == 2 && a.n_iter - k0 - stay >= kMinRanked ? k0 + stay : a.n_iter;
+      for (int k = k0;; ++k) {
+        // positions, and the obstacle search where they have left the reach of
+        // the last one (one more time after the last iteration, for the residual)
+        const bool last = k == a.n_iter;
+        float p[RT][NI][DIMS];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          if ((need & (1u << (3 * rt))) || last) {
+            quad_items(YP[rt], lane, p[rt]);
+            if (__builtin_expect(!still_valid<DIMS>(blk[rt], p[rt]), 0))
+              search_obstacles<DIMS, TRAJ>(sc, blk[rt], p[rt], lane, wm0 + rt * mask_words,
+                                           a.pair_count != nullptr);
+          }
+        if (__builtin_expect(k == stop, 0)) {
+          if (last) {
+            plain = false;
+            break;
+          }
+          bool crowd = false;
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) crowd = crowd || blk[rt].depth > TimeBlock<NI, DIMS>::L;
+          if (any_wave(crowd)) {
+            k0 = k;
+            break;
+          }
+          stay *= 2;
+          stop = a.n_iter - k - stay < kMinRanked ? a.n_iter : k + stay;
+        }
+        const bool lowp = BF16 && (k < a.bf16_iters);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          TimeBlock<NI, DIMS>& b = blk[rt];
+          // push-outs of the row types that may push; nz: those with a nonzero
+          // push-out on some item of the block (the others are left out of the
+          // right-hand side: adding exact zeros to an accumulator that starts
+          // at +0 changes nothing)
+          uint32_t nz = 0;
+          float S[NI][DIMS], dv[NI][DIMS], da[NI][DIMS], r2[NI];
+#pragma unroll
+          for (int n = 0; n < NI; ++n) r2[n] = 0.0f;
+          f4 YV, YA;
+          if (need & (2u << (3 * rt))) YV = chain(rt, 1);
+          if (need & (4u << (3 * rt))) YA = chain(rt, 2);
+          if (need & (1u << (3 * rt))) {
+#pragma unroll
+            for (int n = 0; n < NI; ++n)
+#pragma unroll
+              for (int x = 0; x < DIMS; ++x) S[n][x] = 0.0f;
+            obstacle_pushes<DIMS, false, HIST, TRAJ>(sc, b, p[rt], S, r2, lane, wm0 + rt * mask_words);
+            pairs += b.npairs;
+            if (a.box.on) {
+#pragma unroll
+              for (int n = 0; n < NI; ++n)
+                if (b.ok[n]) box_push<DIMS>(a.box, p[rt][n], S[n], r2[n]);
+            } else if (b.depth == 0) {
+              float left = INFINITY;
+#pragma unroll
+              for (int n = 0; n < NI; ++n) {
+                float d2 = 0.0f;
+#pragma unroll
+                for (int x = 0; x < DIMS; ++x) {
+                  const float e = p[rt][n][x] - b.pref[n][x];
+                  d2 = fmaf(e, e, d2);
+                }
+                left = b.ok[n] ? fminf(left, b.lim[n] - __builtin_amdgcn_sqrtf(d2) * 1.000001f) : left;
+              }
+              Bp[rt] = any_ok[rt] ? budget(left * pscale) : INFINITY;
+            }
+            bool any = false;
+#pragma unroll
+            for (int n = 0; n < NI; ++n)
+#pragma unroll
+              for (int x = 0; x < DIMS; ++x) any = any || (S[n][x] != 0.0f);
+            nz = __ballot(any) != 0ull ? 1u : 0u;
+          }
+          // velocity / acceleration bounds
+          auto bounds = [&](const f4& Y, float wmax, float scale, float (&d)[NI][DIMS], float& B,
+                            uint32_t bit) {
+            float wv[NI][DIMS];
+            quad_items(Y, lane, wv);
+            float m = 0.0f;
+            bool over = false;
+            const float wcap = fminf(wmax * wmax, 3.402823466e38f);  // (an infinite |w|^2 is over any bound)
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {
+              float ww = 0.0f;
+#pragma unroll
+              for (int x = 0; x < DIMS; ++x) ww = fmaf(wv[n][x], wv[n][x], ww);
+              over = over || (b.ok[n] && !(ww <= wcap));
+              m = b.ok[n] ? fmaxf(m, ww) : m;
+            }
+            if (__ballot(over) != 0ull) {
+              nz |= bit;
+              B = -1.0f;
+#pragma unroll
+              for (int n = 0; n < NI; ++n) {
+#pragma unroll
+                for (int x = 0; x < DIMS; ++x) d[n][x] = 0.0f;
+                if (b.ok[n]) bound_push<DIMS>(wv[n], wmax, d[n], r2[n]);
+              }
+            } else {
+              // (v_sqrt_f32 is within 1 ulp)
+              B = any_ok[rt] ? budget((wmax * 0.999999f - __builtin_amdgcn_sqrtf(m) * 1.000001f) * scale)
+                             : INFINITY;
+            }
+          };
+          if (need & (2u << (3 * rt))) bounds(YV, a.vmax, a.bscale[1], dv, Bv[rt], 2u);
+          if (need & (4u << (3 * rt))) bounds(YA, a.amax, a.bscale[2], da, Ba[rt], 4u);
+          block_rhs(rt, k, lowp, nz, S, dv, da, r2);
+        }
+        __syncthreads();
+        const f4 xold = xb;
+        iterate(k, lowp, std::false_type{});
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) YP[rt] = chain(rt, 0);
+        // the budgets of a sample shrink by its largest coefficient change
+        // (rounded up)
+        float m = 0.0f;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) m = fmaxf(m, fabsf(xb[r] - xold[r]));
+        const float dl = quad_max(m) * 1.000002f;
+        X += dl;
+        need = 0;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          Bp[rt] -= dl;
+          Bv[rt] -= dl;
+          Ba[rt] -= dl;
+          need |= (__ballot(!(Bp[rt] >= 0.0f)) != 0ull ? 1u << (3 * rt) : 0u) |
+                  (__ballot(!(Bv[rt] >= 0.0f)) != 0ull ? 2u << (3 * rt) : 0u) |
+                  (__ballot(!(Ba[rt] >= 0.0f)) != 0ull ? 4u << (3 * rt) : 0u);
+        }
+      }
+      if (DIMS == 2 && plain) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int i = 0; i < NI; ++i) blk[rt].lim[i] = -1.0f;
+        k0 = plain_loop(k0, std::false_type{});
       }
     }
-
+    if (plain) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        YP[rt] = chain(rt, 0);
+        float p[NI][DIMS];
+        quad_items(YP[rt], lane, p);
+        if (!still_valid<DIMS>(blk[rt], p))
+          near_obstacles<DIMS, TRAJ>(sc, blk[rt], p, lane, wm0 + rt * mask_words, nm[rt]);
+      }
+    }
     // ---- residual and smoothness cost of the returned iterate -----------------------
     {
-      float* fin = sm + l.fin;
-      // segment of the path-following term: start p0 -> goal pf of this problem
-      float sg[DIMS], ug[DIMS], iuu = 0.0f;
-      if (a.cost.kind != 0) {
-        float uu = 0.0f;
-  #pragma unroll
-        for (int x = 0; x < DIMS; ++x) {
-          sg[x] = bc[x * 6 + 0];
-          ug[x] = bc[x * 6 + 3] - sg[x];
-          uu = fmaf(ug[x], ug[x], uu);
-        }
-        iuu = uu > 0.0f ? 1.0f / uu : 0.0f;
-      }
+      // (the lane's places, worked out again rather than held over the iterations)
+      int le = lane;
+      asm volatile("" : "+v"(le));
+      const int q = le >> 4, col = le & 15, cs = col / AS, cx = col % AS;
+      const bool colok = (cx < DIMS) && (cs < ns);
+      const ConstArgs z = late(args);
+      const CostArgs cost{z->cost.kind,    z->cost.w_acc,     z->cost.w_curv, z->cost.w_path,
+                          z->cost.w_steer, z->cost.wheelbase, z->cost.eps};
+      {
+        const float* bc = z->bc + prob * z->bc_stride;
+        float* fin = sm + l.fin;
+        // segment of the path-following term: start p0 -> goal pf of this problem
+        float sg[DIMS], ug[DIMS], iuu = 0.0f;
+        if (cost.kind != 0) {
+          float uu = 0.0f;
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const TimeBlock<NI, DIMS>& b = blk[rt];
-        float p[NI][DIMS], v[NI][DIMS], ac[NI][DIMS], S[NI][DIMS], r2[NI];
-        quad_items(YP[rt], lane, p);
-        quad_items(chain(rt, 1), lane, v);
-        quad_items(chain(rt, 2), lane, ac);
-#pragma unroll
-        for (int n = 0; n < NI; ++n) {
-          r2[n] = 0.0f;
-#pragma unroll
-          for (int x = 0; x < DIMS; ++x) S[n][x] = 0.0f;
-        }
-        obstacle_pushes<DIMS, true, true, TRAJ>(sc, b, p, S, r2, lane, wm0 + rt * mask_words);
-        pairs += b.npairs;
-#pragma unroll
-        for (int n = 0; n < NI; ++n) {
-          float cc = 0.0f;
-          if (b.ok[n]) {
-            float d[DIMS];
-            bound_push<DIMS>(v[n], a.vmax, d, r2[n]);
-            bound_push<DIMS>(ac[n], a.amax, d, r2[n]);
-            if (a.box.on) box_push<DIMS>(a.box, p[n], S[n], r2[n]);
+          for (int x = 0; x < DIMS; ++x) {
+            sg[x] = bc[x * 6 + 0];
+            ug[x] = bc[x * 6 + 3] - sg[x];
+            uu = fmaf(ug[x], ug[x], uu);
           }
-          if (a.cost.kind == 0) {
-#pragma unroll
-            for (int x = 0; x < DIMS; ++x) cc = fmaf(ac[n][x], ac[n][x], cc);
-          } else {
-            cc = weighted_cost<DIMS>(p[n], v[n], ac[n], a.cost, sg, ug, iuu);
-          }
-          float* f = fin + 2 * (b.t[n] * SPB + cs);
-          if (AS <= 4 || cx < 4) {  // lanes without items own no slot
-            f[0] = b.ok[n] ? r2[n] : 0.0f;
-            f[1] = b.ok[n] ? cc : 0.0f;
-          }
+          iuu = uu > 0.0f ? 1.0f / uu : 0.0f;
         }
-      }
-    }
-    __syncthreads();
-    if (tid < ns) {
-      const int s = tid;
-      float r2 = 0.0f, cc = 0.0f;
-      // (16 steps' reads in flight; the slots past the horizon hold zeros, and
-      // neither sum is ever -0)
-      for (int t = 0; t < K; t += 16) {
-        float2 f[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-          f[u] = *reinterpret_cast<const float2*>(sm + l.fin + 2 * ((t + u) * SPB + s));
+        for (int rt = 0; rt < RT; ++rt) {
+          const TimeBlock<NI, DIMS>& b = blk[rt];
+          float p[NI][DIMS], v[NI][DIMS], ac[NI][DIMS], S[NI][DIMS], r2[NI];
+          quad_items(YP[rt], lane, p);
+          quad_items(chain(rt, 1), lane, v);
+          quad_items(chain(rt, 2), lane, ac);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          r2 += f[u].x;
-          cc += f[u].y;
+          for (int n = 0; n < NI; ++n) {
+            r2[n] = 0.0f;
+#pragma unroll
+            for (int x = 0; x < DIMS; ++x) S[n][x] = 0.0f;
+          }
+          if (plain) near_pushes<DIMS, true, true, TRAJ>(sc, b, p, S, r2, lane, wm0 + rt * mask_words, nm[rt]);
+          else obstacle_pushes<DIMS, true, true, TRAJ>(sc, b, p, S, r2, lane, wm0 + rt * mask_words);
+          pairs += b.npairs;
+#pragma unroll
+          for (int n = 0; n < NI; ++n) {
+            float cc = 0.0f;
+            if (b.ok[n]) {
+              float d[DIMS];
+              bound_push<DIMS>(v[n], a.vmax, d, r2[n]);
+              bound_push<DIMS>(ac[n], a.amax, d, r2[n]);
+              if (a.box.on) box_push<DIMS>(a.box, p[n], S[n], r2[n]);
+            }
+            if (cost.kind == 0) {
+#pragma unroll
+              for (int x = 0; x < DIMS; ++x) cc = fmaf(ac[n][x], ac[n][x], cc);
+            } else {
+              cc = weighted_cost<DIMS>(p[n], v[n], ac[n], cost, sg, ug, iuu);
+            }
+            float* f = fin + 2 * ((16 * (w + TW * rt) + 4 * q + NI * cx + n) * SPB + cs);
+            if (AS <= 4 || cx < 4) {  // lanes without items own no slot
+              f[0] = b.ok[n] ? r2[n] : 0.0f;
+              f[1] = b.ok[n] ? cc : 0.0f;
+            }
+          }
         }
       }
-      const float r = sqrtf(r2);
-      const int64_t nb = prob * a.n_stride + s0 + s;
-      const int64_t dense = static_cast<int64_t>(prob) * a.N + s0 + s;
-      if (a.resid) a.resid[nb] = r;
-      if (a.c1) a.c1[nb] = cc;
-      if (a.resid2) a.resid2[dense] = r;
-      if (a.c12) a.c12[dense] = cc;
-    }
-    if (a.pair_count && lane == 0) atomicAdd(a.pair_count, static_cast<unsigned long long>(pairs));
-    if (w == 0 && colok) {
-      float* dst = a.xi_out + prob * a.xi_out_stride + static_cast<int64_t>(s0 + cs) * D + cx * nv;
-      float* dst2 = a.xi_out2 ? a.xi_out2 + (static_cast<int64_t>(prob) * a.N + s0 + cs) * D + cx * nv
-                              : nullptr;
-  #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int c = coef_of(q, r);
-        if (c < nv) {
-          dst[c] = xb[r];
-          if (dst2) dst2[c] = xb[r];
+      __syncthreads();
+      if (tid < ns) {
+        const int s = tid;
+        float r2 = 0.0f, cc = 0.0f;
+        // (16 steps' reads in flight; the slots past the horizon hold zeros, and
+        // neither sum is ever -0)
+        for (int t = 0; t < K; t += 16) {
+          float2 f[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            f[u] = *reinterpret_cast<const float2*>(sm + l.fin + 2 * ((t + u) * SPB + s));
+#pragma unroll
+          for (int u = 0; u < 16; ++u) {
+            r2 += f[u].x;
+            cc += f[u].y;
+          }
+        }
+        const float r = sqrtf(r2);
+        const int64_t nb = prob * z->n_stride + s0 + s;
+        const int64_t dense = static_cast<int64_t>(prob) * z->N + s0 + s;
+        if (z->resid) z->resid[nb] = r;
+        if (z->c1) z->c1[nb] = cc;
+        if (z->resid2) z->resid2[dense] = r;
+        if (z->c12) z->c12[dense] = cc;
+      }
+      if (a.pair_count && lane == 0) atomicAdd(a.pair_count, static_cast<unsigned long long>(pairs));
+      if (w == 0 && colok) {
+        float* dst = z->xi_out + prob * z->xi_out_stride + static_cast<int64_t>(s0 + cs) * D + cx * nv;
+        float* dst2 = z->xi_out2 ? z->xi_out2 + (static_cast<int64_t>(prob) * z->N + s0 + cs) * D + cx * nv
+                                : nullptr;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int c = coef_of(q, r);
+          if (c < nv) {
+            dst[c] = xb[r];
+            if (dst2) dst2[c] = xb[r];
+          }
         }
       }
     }
@@ -1617,14 +2010,14 @@ __global__ __launch_bounds__(MAXT, RT == 1 ? 4 : 2) void project_kernel(ProjArgs
   const int G = gridDim.x;
   int lb = blockIdx.x;
   if ((G & 7) == 0) lb = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
-  project_block<DIMS, AS, RT, MAXT, BF16, LOOP, false, false, C3>(a, lb, G, total);
+  project_block<DIMS, AS, RT, MAXT, BF16, LOOP, false, false, C3>(a, kernel_args(), lb, G, total);
 }
 
 // The default shape with the per-iteration residual history (HIST, one
 // problem) and/or obstacles given by their paths (TRAJ); one block per tile.
 template <int DIMS, int MAXT, bool BF16, bool HIST, bool TRAJ, bool C3 = true>
 __global__ __launch_bounds__(MAXT, 4) void project_special_kernel(ProjArgs a, int total) {
-  project_block<DIMS, 4, 1, MAXT, BF16, false, HIST, TRAJ, C3>(a, blockIdx.x, 1, total);
+  project_block<DIMS, 4, 1, MAXT, BF16, false, HIST, TRAJ, C3>(a, kernel_args(), blockIdx.x, 1, total);
 }
 
 // Descriptor table (heterogeneous requests sharing n_steps): task t owns
@@ -1639,8 +2032,10 @@ __global__ __launch_bounds__(MAXT, 4) void project_task_kernel(const ProjArgs* t
     if (prefix[mid] <= static_cast<int>(blockIdx.x)) lo = mid;
     else hi = mid;
   }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  const ConstArgs args = reinterpret_cast<ConstArgs>(reinterpret_cast<uintptr_t>(tasks + lo));
   project_block<DIMS, 4, 1, MAXT, BF16, false, false, false, C3>(
-      tasks[lo], static_cast<int>(blockIdx.x) - prefix[lo], 1, tasks[lo].blocks_per_problem);
+      tasks[lo], args, static_cast<int>(blockIdx.x) - prefix[lo], 1, tasks[lo].blocks_per_problem);
 }
 
 // ---------------------------------------------------------------------------
