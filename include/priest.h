@@ -307,10 +307,10 @@ int32_t priest_plan_batch(priest_problem* p, int32_t n_problems, const float* bc
  * that share all (problem, group) pairs of the launch for a grid of resident
  * blocks).  Every shape gives bit-identical results.  By default the
  * library times every candidate the first time a problem handle meets a new
- * (N, n_problems, sampling mode, precision) - one warm-up of one iteration,
- * then two timed launches (four of the fastest shapes) of a shortened (<= 24
- * iteration) copy of the real launch, outputs redirected to scratch - and
- * keeps the fastest.  That first call
+ * (N, n_problems, sampling mode, precision) - one warm-up of one iteration and
+ * a timed launch of 8, then of the faster shapes two launches of 24 iterations,
+ * whatever the call's own count, outputs redirected to scratch - and keeps the
+ * fastest, for calls of every iteration count.  That first call
  * synchronises the stream (and priest_project allocates N*(D+2) floats of
  * scratch for it).  No tuning happens while the stream is being captured
  * into a graph, or with PRIEST_AUTOTUNE=0 in the environment: the default

@@ -567,8 +567,6 @@ int32_t resolve_tiling(priest_problem* p, const ProjArgs& a, int P, hipStream_t 
   return PRIEST_OK;
 }
 
-ProjArgs trial_args(const ProjArgs& a);
-
 // Picks (and applies) the projection tile shape of a plan loop: before any
 // capture, since timing synchronises the stream; the trial needs the first
 // draw's Cholesky factor, which the loop itself recomputes.
@@ -588,22 +586,6 @@ int32_t plan_tiling(priest_problem* p, PlanArgs& pa, int32_t P, hipStream_t s, T
   if (st != PRIEST_OK) return st;
   apply_tiling(pa.a, *cfg);
   return check_lds(p, pa.a);
-}
-
-// A shortened copy of `a` for timing: at most 24 iterations (keeping BF16
-// iterations if `a` has any, so that the same kernel instance runs).  The first
-// iterations, whose obstacle searches the later ones reuse, are not typical:
-// with 8 of 100, 16 2D problems of 1000 samples got the whole-horizon shape at
-// 27 ms a plan instead of the time-split one at 20.
-ProjArgs trial_args(const ProjArgs& a) {
-  ProjArgs t = a;
-  t.n_iter = std::min(a.n_iter, 24);
-  t.bf16_iters = a.bf16_iters > 0 ? std::max(1, std::min(a.bf16_iters, t.n_iter)) : 0;
-  t.xi_src = nullptr;
-  t.resid2 = nullptr;
-  t.c12 = nullptr;
-  t.xi_out2 = nullptr;
-  return t;
 }
 
 }  // namespace

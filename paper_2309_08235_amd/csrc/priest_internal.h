@@ -155,8 +155,12 @@ struct TileCfg {
 };
 std::vector<TileCfg> tile_candidates(int dims, int K);  // [0] is the default shape
 void apply_tiling(ProjArgs& a, const TileCfg& t);
+// A copy of `a` for timing, of the same length whatever a.n_iter is: one pick
+// holds for all of a problem's iteration counts.
+ProjArgs trial_args(const ProjArgs& a);
 // Times every candidate on `trial` (whose outputs must be safe to overwrite);
-// ms[i] < 0 marks a candidate that does not fit.  Synchronises s.
+// ms[i] < 0 marks one that does not fit or was far off in a short run.
+// Synchronises s.
 hipError_t time_tilings(const ProjArgs& trial, int n_problems, size_t lds_limit, hipStream_t s,
                         const std::vector<TileCfg>& cands, std::vector<float>* ms);
 int pick_tiling(const std::vector<float>& ms);

@@ -9,11 +9,13 @@
 // owns a sample group over the whole horizon (no block barrier per
 // iteration; for batches large enough to fill the chip).  All candidates
 // compute bit-identical results, so the choice only affects time: each
-// candidate runs one warm-up launch of one iteration, then two timed launches of
-// the caller's real arguments (outputs redirected by the caller), with HIP
-// events on the caller's stream; those within kAgain of the fastest run a second
-// pass and keep their faster one, and the fastest candidate is kept (by a 3%
-// margin).
+// candidate runs one warm-up launch of one iteration, then a timed one of
+// kShortTrial iterations; those within kAgain of the fastest (the clocks are
+// still rising then, which costs the first candidates up to a third) are timed
+// twice over kTrial iterations, and the fastest of these is kept (by a 3%
+// margin).  All launches take the caller's real arguments but the iteration
+// count (outputs redirected by the caller), timed by HIP events on the caller's
+// stream.
 #include <algorithm>
 #include <vector>
 
@@ -40,9 +42,28 @@ void apply_tiling(ProjArgs& a, const TileCfg& t) {
   a.blocks_per_problem = (a.N + a.S - 1) / a.S;
 }
 
-// The first pass starts while the clocks are still rising, which costs its first
-// candidates up to a third.
+// kTrial iterations are enough for the searching loop to be typical: with 8 of
+// 100, 16 2D problems of 1000 samples got the whole-horizon shape at 27 ms a plan
+// instead of the time-split one at 20.  The tiles choose their loop as in a launch
+// of kTrialOf iterations.  The pick serves calls of any length, so the trial does
+// not depend on the length of the one that happens to come first.  Over 120 random
+// calls, their shape picked in a shorter one, it took 0.55% more time than the
+// best shape, and the picking call 3.8 ms (two launches of every shape over
+// min(n, 24) iterations, then two more of the near ones: 1.0% and 5.1 ms).
+constexpr int kTrial = 24, kTrialOf = 100, kShortTrial = 8;
 constexpr float kAgain = 1.6f;
+
+ProjArgs trial_args(const ProjArgs& a) {
+  ProjArgs t = a;
+  t.n_iter = kTrial;
+  t.trial_of = kTrialOf;
+  t.bf16_iters = a.bf16_iters > 0 ? kTrial : 0;  // (the same kernel instance)
+  t.xi_src = nullptr;
+  t.resid2 = nullptr;
+  t.c12 = nullptr;
+  t.xi_out2 = nullptr;
+  return t;
+}
 
 hipError_t time_tilings(const ProjArgs& trial, int n_problems, size_t lds_limit, hipStream_t s,
                         const std::vector<TileCfg>& cands, std::vector<float>* ms) {
@@ -50,30 +71,34 @@ hipError_t time_tilings(const ProjArgs& trial, int n_problems, size_t lds_limit,
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t err = hipEventCreate(&e0);
   if (err == hipSuccess) err = hipEventCreate(&e1);
-  // Two passes, each candidate keeping its faster one: in one pass the first
-  // candidate would run while the clocks are still rising and lose to shapes
-  // that are slower at steady clocks.
-  float fastest = -1.0f;  // of the first pass
+  auto timed = [&](ProjArgs a, int iters, float* t) {
+    a.n_iter = std::min(a.n_iter, iters);
+    a.bf16_iters = std::min(a.bf16_iters, iters);
+    if (err == hipSuccess) err = hipEventRecord(e0, s);
+    if (err == hipSuccess) err = launch_project(a, n_problems, s);
+    if (err == hipSuccess) err = hipEventRecord(e1, s);
+    if (err == hipSuccess) err = hipEventSynchronize(e1);
+    if (err == hipSuccess) err = hipEventElapsedTime(t, e0, e1);
+  };
+  std::vector<float> first(cands.size(), -1.0f);
+  float fastest = -1.0f;
+  for (size_t i = 0; i < cands.size() && err == hipSuccess; ++i) {
+    ProjArgs a = trial;
+    apply_tiling(a, cands[i]);
+    if (project_lds_bytes(a) > lds_limit) continue;
+    float t = 0.0f;
+    timed(a, 1, &t);  // warm-up (first use of the instance)
+    timed(a, kShortTrial, &first[i]);
+    if (err == hipSuccess && (fastest < 0.0f || first[i] < fastest)) fastest = first[i];
+  }
   for (int pass = 0; pass < 2 && err == hipSuccess; ++pass)
     for (size_t i = 0; i < cands.size() && err == hipSuccess; ++i) {
+      if (first[i] < 0.0f || first[i] > kAgain * fastest) continue;
       ProjArgs a = trial;
       apply_tiling(a, cands[i]);
-      if (project_lds_bytes(a) > lds_limit) continue;
-      if (pass == 1 && (*ms)[i] > kAgain * fastest) continue;
-      if (pass == 0) {  // warm-up (first use of the instance)
-        ProjArgs w = a;
-        w.n_iter = std::min(a.n_iter, 1);
-        w.bf16_iters = std::min(a.bf16_iters, 1);
-        err = launch_project(w, n_problems, s);
-      }
-      if (err == hipSuccess) err = hipEventRecord(e0, s);
-      for (int r = 0; r < 2 && err == hipSuccess; ++r) err = launch_project(a, n_problems, s);
-      if (err == hipSuccess) err = hipEventRecord(e1, s);
-      if (err == hipSuccess) err = hipEventSynchronize(e1);
       float t = 0.0f;
-      if (err == hipSuccess) err = hipEventElapsedTime(&t, e0, e1);
-      if (err == hipSuccess && ((*ms)[i] < 0.0f || t / 2.0f < (*ms)[i])) (*ms)[i] = t / 2.0f;
-      if (pass == 0 && err == hipSuccess && (fastest < 0.0f || (*ms)[i] < fastest)) fastest = (*ms)[i];
+      timed(a, trial.n_iter, &t);
+      if (err == hipSuccess && ((*ms)[i] < 0.0f || t < (*ms)[i])) (*ms)[i] = t;
     }
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
