@@ -32,7 +32,7 @@ int main() {
 def test_trials_do_not_depend_on_the_first_call(tmp_path):
     src, exe = tmp_path / "trial.hip", str(tmp_path / "trial")
     src.write_text(PROGRAM)
-    subprocess.run([build.HIPCC, *build.FLAGS, "-I", build.CSRC, str(src), build.LIB,
-                    "-Wl,-rpath," + build.PKG, "-o", exe], check=True)
+    subprocess.run([build.HIPCC, *build.FLAGS, "-I", build.CSRC, str(src), "-L" + build.PKG,
+                    "-l:libpriest.so", "-Wl,-rpath," + build.PKG, "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
