@@ -139,7 +139,7 @@ struct priest_problem {
   float bscale[3] = {0.0f, 0.0f, 0.0f};  // ProjArgs::bscale
   std::mutex graph_mu;
   std::vector<GraphEntry> graphs;
-  int device = 0;
+  int device = 0, cus = 0;
   size_t lds_limit = 0;
   // projection tile shape: autotuner results per (N, n_problems, mode, bf16)
   std::mutex tune_mu;
@@ -480,29 +480,6 @@ void skip_problems(int32_t p0, PlanArgs& pa, const float*& noise, priest_plan_ou
   skip(out.c1, ca.N);
 }
 
-// Whether a captured plan loop runs its problems in two halves, side by side:
-// one half's refits, and the end of its projections, where blocks wait for the
-// slowest samples, then overlap the other's projections.  Measured, one chain
-// against two, by the launch's waves over those that the device holds (16 a
-// CU): 0.85 (4 2D problems of 1000 samples) 5.03 -> 5.26 ms, 0.98 (8 3D of
-// 2000) 12.6 -> 12.6, 1.2 (64 3D of 300) 16.9 -> 13.9, 1.7 (8 2D of 1000) 9.8
-// -> 8.4, 2.0 (64 2D of 1000) 69 -> 56, 3.9 (64 3D of 1000) 29.3 -> 29.5, 5.9
-// (96 2D of 2000) 169 -> 168, 7.8 (64 3D of 2000) 52.2 -> 54.5.  Four parts
-// took as long as two.
-bool halves_pay(const ProjArgs& a, int32_t P) {
-  if (P < 2) return false;
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return false;
-  const int spw = 16 / a.axis_slots;
-  const int64_t waves = a.row_tiles == 0
-                            ? static_cast<int64_t>(P) * ((a.N + spw - 1) / spw)
-                            : static_cast<int64_t>(P) * a.blocks_per_problem * (project_threads(a.K, a.row_tiles) / 64);
-  const int64_t held = 16 * static_cast<int64_t>(cus);
-  return waves > held && waves < 3 * held;
-}
-
 // The plan loop captured as two chains of half the problems each, the second
 // one on a stream of its own that forks from s and joins it again.
 int32_t capture_halves(int32_t P, const PlanArgs& pa, const priest_cem_params* c, const float* noise,
@@ -596,6 +573,29 @@ int32_t set_error(int32_t code, const char* msg) { return fail(code, "%s", msg);
 ProjArgs problem_args(const priest_problem* p) { return base_args(p); }
 int problem_bf16_iters(const priest_problem* p, int n_iter) { return bf16_iters(p, n_iter); }
 int32_t problem_check_lds(const priest_problem* p, const ProjArgs& a) { return check_lds(p, a); }
+
+// A captured plan loop may run its problems in two halves, side by side: one
+// half's refits, and the end of its projections, where blocks wait for the
+// slowest samples, then overlap the other's projections.  Measured, one chain
+// against two, by the launch's waves over those that the device holds (16 a
+// CU), 20 CEM iterations of 50 (64 problems: 100) projection iterations:
+//   time-split, 2D: 0.85 5.03 -> 5.26 ms, 1.07 4.23 -> 3.32, 2.1 6.53 -> 5.64, 3.0 9.03 -> 7.91
+//   whole horizon:  1.2 28.1 -> 21.9, 2.2 41.8 -> 34.2, 2.7 50.0 -> 47.8, 3.9 29.3 -> 29.5
+//   its groups drawn from a counter, 2D: 1.2 25.7 -> 22.9, 1.8 32.4 -> 29.5, 2.2 36.8 -> 37.6,
+//     2.7 44.8 -> 47.6; 3D: 1.02 7.2 -> 7.0, 1.8 9.6 -> 8.8, 2.0 10.35 -> 10.26, 2.35 11.6 -> 12.4
+// One iteration has no refit to overlap: 0.34 -> 0.36 ms (2D time-split, 1.07), 0.96 -> 1.08
+// (3D from a counter, 1.02); two gain in the time-split shapes (0.60 -> 0.56, 0.95 -> 0.91) but
+// not with a counter (1.67 -> 1.72, 2.23 -> 2.33), three in both.  Four parts took as long as two.
+bool halves_pay(const ProjArgs& a, int32_t P, int32_t n_cem, int32_t cus) {
+  const bool drawn = a.row_tiles == 0 && a.persistent;  // groups from a counter
+  if (P < 2 || n_cem < (drawn ? 3 : 2)) return false;
+  const int spw = 16 / a.axis_slots;
+  const int64_t waves = a.row_tiles == 0
+                            ? static_cast<int64_t>(P) * ((a.N + spw - 1) / spw)
+                            : static_cast<int64_t>(P) * a.blocks_per_problem * (project_threads(a.K, a.row_tiles) / 64);
+  const int64_t held = 16 * static_cast<int64_t>(cus);
+  return waves > held && waves < (drawn ? 2 : 3) * held;
+}
 }  // namespace priest
 
 extern "C" {
@@ -620,6 +620,7 @@ int32_t priest_init_problem(const priest_problem_desc* desc, void* stream, pries
     if ((d.bc_mask >> i) & 1) p->rowsel[E++] = i;
   p->E = E;
   HIP_TRY(hipGetDevice(&p->device));
+  HIP_TRY(hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device));
   static_scratch_setup(p->device);  // priest_plan_static's workspace on this device
   hipDeviceProp_t prop;
   HIP_TRY(hipGetDeviceProperties(&prop, p->device));
@@ -975,7 +976,7 @@ static int32_t plan_common(priest_problem* p, int32_t P, const float* bc, const 
   // loop is captured as one chain)
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
-  const bool halves = halves_pay(pa.a, P) && !stream_capturing(s) &&
+  const bool halves = halves_pay(pa.a, P, c->n_cem, p->cus) && !stream_capturing(s) &&
                       hipStreamCreateWithFlags(&side, hipStreamNonBlocking) == hipSuccess &&
                       hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
                       hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess;

@@ -164,6 +164,9 @@ ProjArgs trial_args(const ProjArgs& a);
 hipError_t time_tilings(const ProjArgs& trial, int n_problems, size_t lds_limit, hipStream_t s,
                         const std::vector<TileCfg>& cands, std::vector<float>* ms);
 int pick_tiling(const std::vector<float>& ms);
+// Whether a captured loop of n_cem launches like `a` over P problems gains from
+// two chains of half the problems each, on a device of so many CUs (api.hip).
+bool halves_pay(const ProjArgs& a, int32_t P, int32_t n_cem, int32_t cus);
 
 // Unfused projection (unfused.hip): workspace layout in bytes and launcher.
 struct UnfusedLayout {
