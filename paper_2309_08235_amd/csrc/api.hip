@@ -980,6 +980,7 @@ static int32_t plan_common(priest_problem* p, int32_t P, const float* bc, const 
                       hipStreamCreateWithFlags(&side, hipStreamNonBlocking) == hipSuccess &&
                       hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
                       hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess;
+  if (!halves) (void)hipGetLastError();  // (a failed creation is not a launch's error)
   auto release = [&] {
     if (join) (void)hipEventDestroy(join);
     if (fork) (void)hipEventDestroy(fork);
