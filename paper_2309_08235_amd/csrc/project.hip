@@ -1681,9 +1681,9 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args,
 #pragma unroll
           for (int n = 0; n < NI; ++n)
             if (b.ok[n]) {
-              if (a.box.on) box_push<DIMS>(a.box, p[n], S[n], r2[n]);
               bound_push<DIMS>(v[n], a.vmax, dv[n], r2[n]);
               bound_push<DIMS>(ac[n], a.amax, da[n], r2[n]);
+              if (a.box.on) box_push<DIMS>(a.box, p[n], S[n], r2[n]);
             }
           block_rhs(rt, k, lowp, 7u, S, dv, da, r2);
         }
@@ -1787,9 +1787,11 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args,
             obstacle_pushes<DIMS, false, HIST, TRAJ>(sc, b, p[rt], S, r2, lane, wm0 + rt * mask_words);
             pairs += b.npairs;
             if (a.box.on) {
+              // (the history adds the box terms after those of the bounds)
+              [[maybe_unused]] float later = 0.0f;
 #pragma unroll
               for (int n = 0; n < NI; ++n)
-                if (b.ok[n]) box_push<DIMS>(a.box, p[rt][n], S[n], r2[n]);
+                if (b.ok[n]) box_push<DIMS>(a.box, p[rt][n], S[n], HIST ? later : r2[n]);
             } else if (b.depth == 0) {
               float left = INFINITY;
 #pragma unroll
@@ -1844,6 +1846,14 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args,
           };
           if (need & (2u << (3 * rt))) bounds(YV, a.vmax, a.bscale[1], dv, Bv[rt], 2u);
           if (need & (4u << (3 * rt))) bounds(YA, a.amax, a.bscale[2], da, Ba[rt], 4u);
+          if constexpr (HIST)
+            if (a.box.on) {  // (then the position rows are always evaluated)
+#pragma unroll
+              for (int n = 0; n < NI; ++n) {
+                float again[DIMS] = {};
+                if (b.ok[n]) box_push<DIMS>(a.box, p[rt][n], again, r2[n]);
+              }
+            }
           block_rhs(rt, k, lowp, nz, S, dv, da, r2);
         }
         __syncthreads();

@@ -69,3 +69,22 @@ def test_residual_history_rejects_null(P):
         P.priest_project_hist(gp.handle, t32(bc), t32(obs), xi, 5, torch.empty_like(xi), None, None,
                               None)
     gp.close()
+
+
+@pytest.mark.parametrize("cfg,N,n_iter", [("c2", 77, 25), ("c3", 40, 12)])
+def test_bounded_history_is_the_residual_of_each_iterate(P, cfg, N, n_iter):
+    """Entry k adds the same squares in the same order as the residual that a
+    projection of k iterations returns: bounds on the workspace come last."""
+    wl = W.CONFIGS[cfg]
+    say(f"bounded residual history {cfg} N={N} iters={n_iter}")
+    lo, hi = ((-0.3,) * 2, (10.3,) * 2) if wl.dims == 2 else ((3.5,) * 3, (16.5,) * 3)
+    gp = P.Problem.from_workload(wl, s_min=lo, s_max=hi)
+    gp.set_tiling((4, 1, 0))
+    bc, obs = W.scene(wl, 0)
+    xi = t32(3.0 * W.samples(wl, 6, n=N))
+    h = gp.project_hist(t32(bc), t32(obs), xi, n_iter)[3]
+    for k in range(n_iter):
+        r = gp.project(t32(bc), t32(obs), xi, k)[1]
+        torch.cuda.synchronize()
+        assert torch.equal(h[k], r), (k, int((h[k] != r).sum()))
+    gp.close()
