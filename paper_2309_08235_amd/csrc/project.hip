@@ -108,8 +108,8 @@ struct Layout {  // offsets into dynamic LDS, in floats
 
 // rec: obstacle records (three float4 arrays of M, structure of arrays); gp:
 // double-buffered partial right-hand sides (256 per 16-step block); fin: per-(t, sample) residual^2 and c1 of the final pass;
-// cm: per-wave obstacle candidate masks (4 words per 64 obstacles); flag: three
-// words per wave for the choice of the loop; xs: the block's samples; mu/L/z: sampler staging.  NB = 16-step blocks of the
+// cm: per-wave obstacle candidate masks (4 words per 64 obstacles); flag: a
+// word per wave for the choice of the loop; xs: the block's samples; mu/L/z: sampler staging.  NB = 16-step blocks of the
 // launch, SPB = samples per block.
 // MB: partial slots per buffer, a compile-time bound >= NB for the sum
 // (slots NB..MB-1 hold zeros).
@@ -557,20 +557,38 @@ constexpr float kReach = 16.0f, kRoomy = 8.0f;
 //   2D 1000,          100: 1704, 2600, 1634
 //   3D  60,             6:  23, 26, 24;   25: 64, 61, 54;    100: 215, 164, 163
 //   3D 1000,           12: 110, 105, 104; 100: 676, 367, 356
-// With 2 or 6 plain iterations first, 60 obstacles and 12 iterations (2D) took
-// 39.5 and 36.3 us, 140 and 100 255 and 258.  At least kMinRanked iterations, and
-// as many as a block has near obstacles but kMostNear, must be left: with 180 and
-// 140 obstacles at 25 iterations 113 and 87 us for kMostNear = 3, 121 and 87 for
-// 4, 113 and 98 for 0.
+// (Those with both loops are of four plain iterations first.)  Up to 128 obstacles,
+// and in 3D, a search is cheap enough for one: a served batch of 8 to 128 obstacles
+// took 9.48 ms with one, 9.62 with two, 10.1 with four, and 3D scenes of 8 to 300 at
+// 12 to 110 iterations 1 to 3% less; 300 obstacles in the plane at 20 and 30
+// iterations want the four, 6% less.  At least min_ranked iterations, and as many as a
+// block has near obstacles but most_near, must be left: with eight groups of 300
+// samples among 106 obstacles at 10 x 15 iterations 1022 us for 3, 913 for 12, with 6 x
+// 800 among 74 at 16 185 and 166, in 3D 1000 at 12 154 and 130; but with 180 and 140
+// obstacles (4 samples a block) at 25 iterations 113 and 87 us for 3, 121 and 87 for 4,
+// 113 and 98 for 0.  (8 samples a block: a wave has more obstacles near it, each near
+// fewer of its items.)  Paths are read from memory in every plain iteration, so there
+// only a crowd keeps from searching (120 obstacles, 24 iterations: 160 us with 3, 130
+// without the limit; 883 in 3D at 20: 265, 185; searching crowds too, 379 at 23 took
+// 677 us for 533).  With 40 and 90 obstacles in the plane and 6 iterations, searching
+// in the last five costs up to a tenth more than not at all; in 3D it saves a tenth.
 // The first look for crowded tiles in the searching loop comes after kBackFirst
 // iterations: 180 obstacles (2D), 25 and 100 iterations, 116 and 402 us, without
 // any 135 and 485; a 20 x 100 plan of 50 2.88 and 2.83 ms.  (After 2 and 4: 115
 // and 117 us, 2.89 ms.)  In 3D searching was the faster also with 1000.
-constexpr int kPlainFirst = 4, kMinRanked = 4, kMostNear = 3, kBackFirst = 8;
+constexpr int kBackFirst = 8;
+constexpr int min_ranked(int dims) { return dims == 2 ? 8 : 4; }
+constexpr bool cheap_search(int dims, int M) { return dims == 3 || M <= 128; }
+constexpr int plain_first(int dims, int M) { return cheap_search(dims, M) ? 1 : 4; }
+constexpr int most_near(int dims, int M, int axis_slots, bool paths) {
+  return paths ? 1 << 20 : cheap_search(dims, M) || axis_slots == 2 ? 12 : 3;
+}
 
 // Obstacles an item keeps between iterations: its nearest ones, in registers.
-// (3D: a third one spills registers, which alone takes 0.7 us a launch.)
-constexpr int lane_slots(int dims) { return dims == 2 ? 4 : 2; }
+// (3D: a third one spills registers, which takes 0.7 us a launch, but with two many
+// more items are crowded: 1000 spheres, some of them moving, 100 iterations 343 us
+// with three, 560 with two.)
+constexpr int lane_slots(int dims) { return dims == 2 ? 4 : 3; }
 
 // One 16-step time block of a wave of the time-split shapes: its items, and
 // the memory of its last obstacle search: every item's position at that time
@@ -1646,7 +1664,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args,
     // stopped at: the last, or (choose) the first the searching loop is to do.
     auto plain_loop = [&](int k, auto choose) __attribute__((always_inline)) {
       constexpr bool CHOOSE = decltype(choose)::value;
-      int stay = kPlainFirst, next = a.n_iter - kPlainFirst < kMinRanked ? a.n_iter : kPlainFirst;
+      int stay = plain_first(DIMS, M), next = a.n_iter - stay < min_ranked(DIMS) ? a.n_iter : stay;
       while (k < a.n_iter) {
         const bool lowp = BF16 && (k < a.bf16_iters);
 #pragma unroll
@@ -1700,18 +1718,18 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args,
               quad_items(chain(rt, 0), lane, p);
               uint32_t* wm = wm0 + rt * mask_words;
               if (!still_valid<DIMS>(blk[rt], p)) near_obstacles<DIMS, TRAJ>(sc, blk[rt], p, lane, wm, nm[rt]);
-              crowd = crowd || static_cast<int>(nm[rt].n) > ahead - k + kMostNear ||
+              crowd = crowd || static_cast<int>(nm[rt].n) > ahead - k + most_near(DIMS, M, AS, TRAJ) ||
                       crowded<DIMS, TRAJ>(sc, blk[rt], p, lane, wm, nm[rt]);
             }
             if (!any_wave(crowd)) break;
             stay *= 2;
-            next = a.n_iter - k - stay < kMinRanked ? a.n_iter : k + stay;
+            next = a.n_iter - k - stay < min_ranked(DIMS) ? a.n_iter : k + stay;
           }
       }
       return k;
     };
     // ---- projection iterations ---------------------------------------------------
-    // The plain loop first (kPlainFirst), then the searching one, unless an item
+    // The plain loop first (plain_first), then the searching one, unless an item
     // is crowded, or what is left would not earn the search of the block with the
     // most near obstacles; then the question is put again after twice as many
     // iterations.  In 2D a tile found crowded after kBackFirst, twice as many, ...
@@ -1735,7 +1753,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args,
 #pragma unroll
         for (int i = 0; i < NI; ++i) blk[rt].lim[i] = -1.0f;
       }
-      int stay = kBackFirst, stop = DIMS == 2 && a.n_iter - k0 - stay >= kMinRanked ? k0 + stay : a.n_iter;
+      int stay = kBackFirst, stop = DIMS == 2 && a.n_iter - k0 - stay >= min_ranked(DIMS) ? k0 + stay : a.n_iter;
       for (int k = k0;; ++k) {
         // positions, and the obstacle search where they have left the reach of
         // the last one (one more time after the last iteration, for the residual)
@@ -1762,7 +1780,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, ConstArgs args,
             break;
           }
           stay *= 2;
-          stop = a.n_iter - k - stay < kMinRanked ? a.n_iter : k + stay;
+          stop = a.n_iter - k - stay < min_ranked(DIMS) ? a.n_iter : k + stay;
         }
         const bool lowp = BF16 && (k < a.bf16_iters);
 #pragma unroll

@@ -56,6 +56,15 @@ def test_every_iteration_count_has_the_same_bits(P, dims, M, crowd, K, N):
     _same(_project(P, wl, bc, obs, t32(W.samples(wl, 3, n=N)), EDGES), f"{dims}D M={M}")
 
 
+@pytest.mark.parametrize("M,crowd", [(5, 4), (129, 66), (300, 0)])
+def test_every_iteration_count_in_space(P, M, crowd):
+    """In 3D the loop may change after 1, 3, 7, 15 and 31 iterations, with 4 left."""
+    print(f"[gpu-case] loop choice: 3D edges M={M} crowd={crowd}", flush=True)
+    wl, bc, obs = _scene(3, M, crowd, 12)
+    counts = [1, 2, 4, 5, 6, 7, 8, 11, 12, 14, 15, 18, 19, 20, 31, 34, 35, 36]
+    _same(_project(P, wl, bc, obs, t32(W.samples(wl, 3, n=10)), counts), f"3D M={M}")
+
+
 @pytest.mark.parametrize("dims", [2, 3])
 @pytest.mark.parametrize("kind", ["radii", "bounds", "bf16"])
 @pytest.mark.parametrize("M,crowd", [(12, 0), (150, 40)])
