@@ -583,18 +583,26 @@ int32_t problem_check_lds(const priest_problem* p, const ProjArgs& a) { return c
 //   whole horizon:  1.2 28.1 -> 21.9, 2.2 41.8 -> 34.2, 2.7 50.0 -> 47.8, 3.9 29.3 -> 29.5
 //   its groups drawn from a counter, 2D: 1.2 25.7 -> 22.9, 1.8 32.4 -> 29.5, 2.2 36.8 -> 37.6,
 //     2.7 44.8 -> 47.6; 3D: 1.02 7.2 -> 7.0, 1.8 9.6 -> 8.8, 2.0 10.35 -> 10.26, 2.35 11.6 -> 12.4
-// One iteration has no refit to overlap: 0.34 -> 0.36 ms (2D time-split, 1.07), 0.96 -> 1.08
-// (3D from a counter, 1.02); two gain in the time-split shapes (0.60 -> 0.56, 0.95 -> 0.91) but
-// not with a counter (1.67 -> 1.72, 2.23 -> 2.33), three in both.  Four parts took as long as two.
+// One CEM iteration has no refit to overlap: 0.34 -> 0.36 ms (2D time-split, 1.07), 0.96 -> 1.08
+// (3D from a counter, 1.02).  The fork and join cost 40 to 80 us a replay, which the time-split
+// shapes gain back by n_cem (n_iter + 10) = 120 (24 2D problems of 704 samples and 22 steps, 1.03:
+// n_cem, n_iter 2, 5 245 -> 290 us; 4, 5 411 -> 425; 3, 15 523 -> 527; 8, 5 736 -> 713; 3, 40 765 ->
+// 756; 9 of 1000 and 100, 1.92: 2, 15 418 -> 427; 2, 40 725 -> 697; 3, 40 1011 -> 924), one wave a
+// group by half of that (3, 15: 1099 -> 991 us, 2160 -> 1808).  From a counter two iterations lose
+// (1.67 -> 1.72 ms, 2.23 -> 2.33), and few problems do: 12 3D ones of 1500 samples (1.10) 8, 15
+// 2.54 -> 2.94 ms, 18, 50 7.09 -> 7.22, 17 of 1200 (1.25) 2.54 -> 2.87, 7.17 -> 7.22; 24 of 1200
+// (1.76) 3.14 -> 3.02, 8.63 -> 8.11.  78 2D ones of 800 (1.9) at 8, 15 6.26 -> 6.35, 60 of 1000
+// (1.83) 6.80 -> 6.36.  Four parts took as long as two.
 bool halves_pay(const ProjArgs& a, int32_t P, int32_t n_cem, int32_t cus) {
   const bool drawn = a.row_tiles == 0 && a.persistent;  // groups from a counter
-  if (P < 2 || n_cem < (drawn ? 3 : 2)) return false;
+  if (P < (drawn ? 20 : 2) || n_cem < (drawn ? 3 : 2)) return false;
+  if (static_cast<int64_t>(n_cem) * (a.n_iter + 10) < (a.row_tiles == 0 && !drawn ? 60 : 120)) return false;
   const int spw = 16 / a.axis_slots;
   const int64_t waves = a.row_tiles == 0
                             ? static_cast<int64_t>(P) * ((a.N + spw - 1) / spw)
                             : static_cast<int64_t>(P) * a.blocks_per_problem * (project_threads(a.K, a.row_tiles) / 64);
   const int64_t held = 16 * static_cast<int64_t>(cus);
-  return waves > held && waves < (drawn ? 2 : 3) * held;
+  return waves > held && 8 * waves < (drawn ? 15 : 24) * held;
 }
 }  // namespace priest
 

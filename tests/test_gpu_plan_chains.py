@@ -41,7 +41,7 @@ cus = torch.cuda.get_device_properties(0).multi_processor_count
 n_problems = 9
 n = 8 * ((24 * cus) // (7 * n_problems))
 wl = W.with_changes(W.C2, n_obs=10, n_samples=n, n_proj=W.default_n_proj(n),
-                    n_elite=W.default_n_elite(n), n_proj_iters=8)
+                    n_elite=W.default_n_elite(n), n_proj_iters=30)
 gp = P.Problem.from_workload(wl)
 gp.set_tiling((2, 1, 0))
 t32 = lambda x: torch.as_tensor(np.ascontiguousarray(x), dtype=torch.float32).cuda()

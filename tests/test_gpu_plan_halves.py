@@ -60,3 +60,38 @@ def test_captured_batch_equals_eager(base, shape, n_problems, n, given, cma):
             assert torch.equal(v, out_g[k]), k
         assert torch.equal(mu_e, mu_g) and torch.equal(cov_e, cov_g)
     gp.close()
+
+
+@pytest.mark.parametrize("base,shape,n_problems,n,cma", [
+    (W.C2, (2, 1, 0), 7, 901, False),    # 5537 waves
+    (W.C2, (2, 0, 1), 63, 600, True),    # 4725
+    (W.C3, (4, 0, 1), 21, 850, False),   # 4473
+], ids=["2d time-split", "2d counter", "3d counter"])
+def test_longer_captured_batch_equals_eager(base, shape, n_problems, n, cma):
+    """As above, with the iterations that earn the second chain, and no given noise."""
+    print(f"halves: {base.dims}d {shape} P={n_problems} N={n}, 30 iterations", flush=True)
+    wl = W.with_changes(base, n_obs=min(base.n_obs, 20), n_samples=n, n_proj=W.default_n_proj(n),
+                        n_elite=W.default_n_elite(n), n_proj_iters=30)
+    gp = P.Problem.from_workload(wl)
+    gp.set_tiling(shape)
+    scenes = [W.scene(wl, 3 + i) for i in range(n_problems)]
+    bc, obs = t32(np.stack([s[0] for s in scenes])), t32(np.stack([s[1] for s in scenes]))
+    cem = _cem(wl, n_cem=3, **({"update": 1} if cma else {}))
+    mu0 = t32(np.stack([W.initial_mean(wl)] * n_problems))
+    cov0 = t32(np.stack([W.initial_cov(wl)] * n_problems))
+    stream, ws = torch.cuda.Stream(), gp.workspace(cem, n_problems)
+    out, mu, cov = gp.plan_outputs(cem, n_problems, full=True), mu0.clone(), cov0.clone()
+    for _ in range(3):
+        mu_e, cov_e = mu0.clone(), cov0.clone()
+        want = gp.plan_batch(n_problems, bc, obs, cem, mu_e, cov_e, seed=5)
+        mu.copy_(mu0), cov.copy_(cov0)
+        for v in out.values():
+            v.zero_()
+        torch.cuda.synchronize()
+        gp.plan_batch(n_problems, bc, obs, cem, mu, cov, seed=5, out=out, workspace=ws, use_graph=True,
+                      stream=stream)
+        torch.cuda.synchronize()
+        for k, v in want.items():
+            assert torch.equal(v, out[k]), k
+        assert torch.equal(mu_e, mu) and torch.equal(cov_e, cov)
+    gp.close()

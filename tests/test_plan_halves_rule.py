@@ -53,3 +53,32 @@ def test_two_chains_only_where_they_pay(tmp_path):
                     "-l:libpriest.so", "-Wl,-rpath," + build.PKG, "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_loops_of_little_work_take_one_chain(tmp_path):
+    """The fork and join have to be earned back: by n_cem (n_iter + 10) = 120, or
+    60 with one wave a group, and with a counter by 20 problems."""
+    program = PROGRAM[:PROGRAM.index("int main")].replace("a.n_iter = 50", "a.n_iter = iters")
+    program = program.replace("int bad = 0;", "int bad = 0, iters;") + """
+int main() {
+  iters = 5;
+  for (int cem : {2, 4, 7}) want(false, 9, cem, 2, 100, 1000, TileCfg{2, 1, 0});
+  want(true, 9, 8, 2, 100, 1000, TileCfg{2, 1, 0});
+  want(false, 22, 3, 3, 100, 1000, TileCfg{4, 0, 0});
+  want(true, 22, 4, 3, 100, 1000, TileCfg{4, 0, 0});
+  iters = 30;
+  want(false, 9, 2, 2, 100, 1000, TileCfg{2, 1, 0});
+  want(true, 9, 3, 2, 100, 1000, TileCfg{2, 1, 0});
+  want(false, 19, 20, 3, 100, 1200, TileCfg{4, 0, 1});
+  want(true, 20, 20, 3, 100, 1200, TileCfg{4, 0, 1});
+  want(true, 24, 3, 3, 100, 1200, TileCfg{4, 0, 1});   // 1.76
+  want(false, 26, 20, 3, 100, 1200, TileCfg{4, 0, 1});  // 1.90
+  return bad != 0;
+}
+"""
+    src, exe = tmp_path / "little.hip", str(tmp_path / "little")
+    src.write_text(program)
+    subprocess.run([build.HIPCC, *build.FLAGS, "-I", build.CSRC, str(src), "-L" + build.PKG,
+                    "-l:libpriest.so", "-Wl,-rpath," + build.PKG, "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
