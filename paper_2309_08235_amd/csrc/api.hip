@@ -984,11 +984,12 @@ static int32_t plan_common(priest_problem* p, int32_t P, const float* bc, const 
   // loop is captured as one chain)
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
-  const bool halves = halves_pay(pa.a, P, c->n_cem, p->cus) && !stream_capturing(s) &&
+  const bool wanted = halves_pay(pa.a, P, c->n_cem, p->cus) && !stream_capturing(s);
+  const bool halves = wanted &&
                       hipStreamCreateWithFlags(&side, hipStreamNonBlocking) == hipSuccess &&
                       hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
                       hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess;
-  if (!halves) (void)hipGetLastError();  // (a failed creation is not a launch's error)
+  if (wanted && !halves) (void)hipGetLastError();  // (a failed creation is not a launch's error)
   auto release = [&] {
     if (join) (void)hipEventDestroy(join);
     if (fork) (void)hipEventDestroy(fork);

@@ -55,6 +55,15 @@ cov0 = t32(np.stack([W.initial_cov(wl)] * n_problems))
 stream, ws = torch.cuda.Stream(), gp.workspace(cem, n_problems)
 out, mu, cov = gp.plan_outputs(cem, n_problems, full=True), mu0.clone(), cov0.clone()
 refuse.value = refused
+if sys.argv[6] == "pending":  # an error that someone else left is reported, not swallowed
+    hip.hipSetDevice(1 << 20)
+    try:
+        gp.plan_batch(n_problems, bc, obs, cem, mu, cov, seed=5, noise=noise, out=out, workspace=ws,
+                      use_graph=True, stream=stream)
+    except P.PriestError as e:
+        print("reported:", e, flush=True)
+        sys.exit(0)
+    sys.exit("not reported")
 for replay in range(3):
     mu_e, cov_e = mu0.clone(), cov0.clone()
     want = gp.plan_batch(n_problems, bc, obs, cem, mu_e, cov_e, seed=5, noise=noise,
@@ -84,6 +93,19 @@ def test_chains_of_a_captured_batch(tmp_path, gpu_lib, chains, refused, n_cem):
     src.write_text(SHIM)
     child.write_text(CHILD)
     subprocess.run(["gcc", "-shared", "-fPIC", str(src), "-o", shim], check=True)
-    r = subprocess.run([sys.executable, str(child), shim, ROOT, str(chains), str(refused), str(n_cem)],
+    r = subprocess.run([sys.executable, str(child), shim, ROOT, str(chains), str(refused), str(n_cem), ""],
                        capture_output=True, text=True, timeout=110)
     assert r.returncode == 0 and "same outputs" in r.stdout, r.stdout + r.stderr
+
+
+def test_an_error_from_before_a_captured_batch_is_reported(tmp_path, gpu_lib):
+    """One chain creates no stream, so there is no error of its own to take back."""
+    print("[gpu-case] plan chains: an error pending before the call", flush=True)
+    from tests.conftest import ROOT
+    src, shim, child = tmp_path / "shim.c", str(tmp_path / "shim.so"), tmp_path / "child.py"
+    src.write_text(SHIM)
+    child.write_text(CHILD)
+    subprocess.run(["gcc", "-shared", "-fPIC", str(src), "-o", shim], check=True)
+    r = subprocess.run([sys.executable, str(child), shim, ROOT, "1", "0", "1", "pending"],
+                       capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0 and "reported:" in r.stdout, r.stdout + r.stderr
