@@ -408,7 +408,7 @@ int32_t priest_debug_normals(uint64_t seed, uint32_t stream_id, int32_t iter, in
  * ties in the order of the first selection (ascending r, then index).  With
  * proj_idx non-NULL it also writes that first selection [n_proj] (device),
  * ascending r, and takes the sorting path; with NULL it takes the path the
- * plan takes in its other iterations (radix selects where N <= 2048 and
+ * plan takes in its other iterations (selects without a sort where N <= 2048 and
  * n_elite <= 512).  Requires 1 <= n_elite <= n_proj <= N <= 8192.
  * Allocates and frees scratch; synchronises `stream`. */
 int32_t priest_debug_select(int32_t N, int32_t n_proj, int32_t n_elite, const float* r,

@@ -12,6 +12,11 @@
 //   selects of the boundary keys (histograms of the value range, then of the
 //   key range, until at most 32 keys are left) and a ranking of the n_elite
 //   survivors by counting, which select and order exactly the same samples.
+//   3. weights c_m = exp(-(c_aug_m - delta)/gamma), delta = min c_aug;
+//   4. mu' = (1-sigma) mu + sigma sum w xi_bar / sum w,
+//      Sigma' = (1-sigma) Sigma + sigma sum w (xi_bar - mu')(xi_bar - mu')^T / sum w;
+//   5. L = chol(Sigma' + eps I), eps = cov_jitter tr(Sigma')/D, for the next
+//      draw: one wave, a rank-1 MFMA per column.
 //
 // One block on one CU: bound by chains of LDS round trips, barriers and the
 // first fetch of code that a launch runs once.  At N = 1000, 100 elites,
@@ -19,11 +24,7 @@
 // 6k, covariance 7k, factor 9k; before, 39k to 50k by the number of equal
 // keys), at N = 1500, 150 elites, D = 33 60k (15k, 2k, 11k, 12k, 17k; before,
 // 85k to 100k).
-//   3. weights c_m = exp(-(c_aug_m - delta)/gamma), delta = min c_aug;
-//   4. mu' = (1-sigma) mu + sigma sum w xi_bar / sum w,
-//      Sigma' = (1-sigma) Sigma + sigma sum w (xi_bar - mu')(xi_bar - mu')^T / sum w;
-//   5. L = chol(Sigma' + eps I), eps = cov_jitter tr(Sigma')/D, for the next
-//      draw: one wave, a rank-1 MFMA per column.
+//
 // Every sum runs in a fixed order, so results are bitwise reproducible.
 #include "priest_internal.h"
 #include "quotient.h"
@@ -265,9 +266,9 @@ __device__ __forceinline__ void bitonic_sort_keys(unsigned long long* a, int n) 
 
 // ---- selection without a full sort ------------------------------------------
 // Used when the ordered constraint-elite set is not asked for: the two
-// selections of steps 1 and 2 as exact radix selects (the k-th smallest key,
-// 8 bits per pass from the top), then the n_elite survivors ranked by
-// counting.  Selects exactly the samples, in exactly the order, of the two
+// selections of steps 1 and 2 as selects of the k-th smallest key (select_kth: a
+// histogram of the value range, then of the crossing bin's key range, until at most
+// 32 keys are left to rank), then the n_elite survivors ranked by counting.  Selects exactly the samples, in exactly the order, of the two
 // stable sorts: step 1 keeps the lowest (r key, index), step 2 the lowest
 // (c_aug key, r key, index).
 

@@ -18,7 +18,8 @@
 //             every axis of 4/AS (sample, t) items per time block
 //   push-out  closed-form alpha/beta/d of each obstacle as a push-out
 //             Delta * max(0, 1/n - 1) (n = scaled distance), summed over the
-//             item's nearest obstacles, kept in registers between iterations;
+//             item's nearest obstacles, kept in registers between iterations (in
+//             the first iterations and in crowded tiles over all near ones);
 //             velocity / acceleration push-outs w * min(0, w_max/|w| - 1)
 //   transpose back to the column layout
 //   RHS       g_partial = W^T delta per 16-step block (MFMA, the sum over t
@@ -33,16 +34,16 @@
 //             which holds after the first step; it avoids cancelling
 //             n_obs |p| against rho F^T F xi_bar in FP32.
 //
-// What bounds it: instruction issue.  A launch of 250 blocks of 7 waves (1000
-// samples, 100 steps) puts two waves on three SIMDs of a CU and one on the
-// fourth; inserted into its loop, a VALU instruction cost 6 cycles, a taken
+// What bounds it: latency and instruction issue.  A launch of 250 blocks of 7
+// waves (1000 samples, 100 steps) puts two waves on three SIMDs of a CU and one
+// on the fourth; inserted into its loop, a VALU instruction cost 6 cycles, a taken
 // branch 20, a dependent MFMA 36, an LDS round trip 61 and a barrier nothing.
 // So the loop keeps few instructions and branches on the path that paces the
 // barrier: no LDS transposes (they were 24 LDS operations per wave and
 // iteration), no row types that cannot push, no loop over obstacles, half the
 // partial-sum reads in 2D, no coefficient chunk 3 where there is none.  100
-// iterations of 1000 fresh 2D samples, whole call: 224 -> 179 us; a 2D plan of
-// 20 x 100 iterations 4.14 -> 2.96 ms, a 3D one of 2000 samples 6.14 -> 4.13 ms.
+// iterations of 1000 fresh 2D samples, whole call: 223 -> 176 us; a 2D plan of
+// 20 x 100 iterations 4.28 -> 2.81 ms, a 3D one of 2000 samples 6.09 -> 3.64 ms.
 //
 // After the last iteration one more forward + push-out pass evaluates
 // r(xi_bar) and c1 = sum_t |a_t|^2, summed per sample in fixed t order.
@@ -549,29 +550,30 @@ constexpr float kReach = 16.0f, kRoomy = 8.0f;
 
 // The first iterations, in which most items leave the reach of their search, and
 // tiles with crowded items run a loop without searches (plain_loop in
-// project_block).  Kernel time of 1000 samples, a 2D (3D) scene of 10 (20) m, us;
-// with no searching loop, with it alone, and with both:
-//   2D  60 obstacles,   6 iterations:  23.5, 28.9, 23.4;  100: 226, 181, 180
-//   2D 140,            12:  54, 60, 55;   25: 98, 90, 90;    100: 387, 252, 254
-//   2D 250,             6:  43, 80, 42;   25: 136, 210, 137; 100: 490, 665, 505
-//   2D 1000,          100: 1704, 2600, 1634
-//   3D  60,             6:  23, 26, 24;   25: 64, 61, 54;    100: 215, 164, 163
-//   3D 1000,           12: 110, 105, 104; 100: 676, 367, 356
-// (Those with both loops are of four plain iterations first.)  Up to 128 obstacles,
-// and in 3D, a search is cheap enough for one: a served batch of 8 to 128 obstacles
-// took 9.48 ms with one, 9.62 with two, 10.1 with four, and 3D scenes of 8 to 300 at
-// 12 to 110 iterations 1 to 3% less; 300 obstacles in the plane at 20 and 30
-// iterations want the four, 6% less.  At least min_ranked iterations, and as many as a
-// block has near obstacles but most_near, must be left: with eight groups of 300
-// samples among 106 obstacles at 10 x 15 iterations 1022 us for 3, 913 for 12, with 6 x
-// 800 among 74 at 16 185 and 166, in 3D 1000 at 12 154 and 130; but with 180 and 140
-// obstacles (4 samples a block) at 25 iterations 113 and 87 us for 3, 121 and 87 for 4,
-// 113 and 98 for 0.  (8 samples a block: a wave has more obstacles near it, each near
-// fewer of its items.)  Paths are read from memory in every plain iteration, so there
-// only a crowd keeps from searching (120 obstacles, 24 iterations: 160 us with 3, 130
-// without the limit; 883 in 3D at 20: 265, 185; searching crowds too, 379 at 23 took
-// 677 us for 533).  With 40 and 90 obstacles in the plane and 6 iterations, searching
-// in the last five costs up to a tenth more than not at all; in 3D it saves a tenth.
+// project_block).  Kernel time of 1000 samples, a 2D (3D) scene of 10 (20) m with 4
+// samples a block, us; by masks of near obstacles only, by a search in every launch,
+// and with both loops:
+//   2D  60 obstacles,   6 iterations:  24.1, 29.4, 24.1;  12: 39, 43, 39;  100: 234, 187, 185
+//   2D 140,            12:  55, 60, 59;   25: 101, 93, 92;   100: 390, 254, 262
+//   2D 250,             6:  43, 81, 42;   25: 137, 216, 140; 100: 491, 668, 503
+//   2D 1000,          100: 1711, 2598, 1611
+//   3D  60,             6:  22.4, 25.4, 23.4;   25: 67, 64, 57;    100: 219, 169, 165
+//   3D 1000,           12: 111, 107, 104; 100: 678, 368, 336
+// Up to 128 obstacles, and in 3D, a search is cheap enough for one: a served batch of
+// 8 to 128 obstacles took 9.48 ms with one, 9.62 with two, 10.1 with four, and 3D
+// scenes of 8 to 300 at 12 to 110 iterations 1 to 3% less; 300 obstacles in the plane
+// at 20 and 30 iterations want the four, 6% less.  At least min_ranked iterations, and
+// as many as a block has near obstacles but most_near, must be left: with eight groups
+// of 300 samples among 106 obstacles at 10 x 15 iterations 1022 us for 3, 913 for 12,
+// with 6 x 800 among 74 at 16 185 and 166, in 3D 1000 at 12 154 and 130; but with 180
+// and 140 obstacles (4 samples a block) at 25 iterations 113 and 87 us for 3, 121 and
+// 87 for 4, 113 and 98 for 0.  (8 samples a block: a wave has more obstacles near it,
+// each near fewer of its items.)  Paths are read from memory in every plain iteration,
+// so there only a crowd keeps from searching (120 obstacles, 24 iterations: 160 us
+// with 3, 130 without the limit; 883 in 3D at 20: 265, 185; searching crowds too, 379
+// at 23 took 677 us for 533).  With 40 and 90 obstacles in the plane and 6 iterations,
+// searching in the last five costs up to a tenth more than not at all; in 3D it saves
+// a tenth.
 // The first look for crowded tiles in the searching loop comes after kBackFirst
 // iterations: 180 obstacles (2D), 25 and 100 iterations, 116 and 402 us, without
 // any 135 and 485; a 20 x 100 plan of 50 2.88 and 2.83 ms.  (After 2 and 4: 115
@@ -2271,7 +2273,7 @@ __device__ __forceinline__ uint32_t wave_block_cull(const float4* rec, int M, co
 }
 
 // Push-outs of this lane's items in one 16-step block of the whole-horizon
-// shape (the per-pair and per-bound arithmetic of item_push, in the same
+// shape (pair_term, pair_add, bound_push and box_push in the time-split shapes'
 // canonical obstacle order) for the row types in `comp` (bit 0: obstacles
 // and workspace bounds on the positions, bit 1: velocity, bit 2:
 // acceleration); the push-outs of the other row types are zero on every
